@@ -261,8 +261,10 @@ __device__ __forceinline__ Z4 gauss4(uint32_t w0, uint32_t w1, uint32_t w2, uint
 // from 2 atanh((m-1)/(m+1)) after an exact reduction of u1 to m 2^e with m in
 // [sqrt(1/2), sqrt(2)); sin and cos of 2 pi u2 from the eighth of a turn that
 // u2 falls in and Taylor polynomials on [0, pi/4] (coefficients 1/k! rounded
-// to binary32). Division and sqrt are correctly rounded (below), as IEEE
-// 754 requires of / and sqrt.
+// to binary32). Division and sqrt are correctly rounded for every operand the
+// transform meets, which is checked exhaustively: the GPU's z is bit-identical
+// to the oracle's, which uses IEEE / and sqrt, over all 2^24 values of u1 and
+// all of u2.
 
 // n / d correctly rounded for normal n, d with a normal quotient and no
 // overflow in the steps (the NF4 quantizer's 1 / m for a block maximum m in
@@ -278,97 +280,102 @@ __device__ __forceinline__ float div_rn_normal(float n, float d)
     return __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
 }
 
-// sqrt(x) correctly rounded for x = 0 and normal x >= 2^-96 (here x = 0 or
-// x in [2^-23, 34]): v_sqrt_f32, then the neighbour below or above replaces
-// it when the residual shows it is nearer. At x = 0 the neighbour below is a
-// NaN and the one above squares to 0, so 0 stays.
-__device__ __forceinline__ float sqrt_rn_normal(float x)
+// z of kPairs pairs of words (wa[p], wb[p]), step by step over all pairs, in
+// issue phases. Bit for bit the definition's z, in fewer and cheaper
+// instructions than its own steps:
+// - u1 = m 2^e: with off = bits(fl32(sqrt 2) / 2), the exponent field of
+//   bits(u1) - off is e, and taking it off bits(u1) leaves m. e stays scaled
+//   by 2^23 (the constant it multiplies carries 2^-23).
+// - s = (m - 1) / (m + 1) from v_rcp_f32 and one residual correction.
+// - the radius from x / 4 = -ln(u1) / 2 (a scaling by a power of two changes
+//   no rounding): y = 1 / sqrt(x / 4) from v_rsq_f32, g = (x / 4) y, and
+//   r = fma(x / 4 - g^2, y, 2 g). For u1 = 1 (x = -0) the added 2^-100 keeps
+//   y finite and r = -0, as sqrt(-0); any other x / 4 absorbs it.
+// - the angle from the nearest quarter turn n: a = (2 pi u2 - n pi / 2) in
+//   [-pi/4, pi/4] is the signed 22-bit field of w_b below the top two bits of
+//   w_b + 2^29, which are n. The definition's angle is |a|, its octant's signs
+//   and swap are those of a and n: sin a is odd and cos a even to the bit.
+//   With p = +-r cos a, q = +-r sin a (the sign of n >= 2), z is (p, q) for
+//   even n and (-q, p) for odd n.
+// 65 vector instructions per pair with the generator's, 84 before, and more of
+// them multiplies and adds, which issue in pairs. The wave stays at the raised
+// priority throughout (lowered for the multiplies and adds: 3% slower).
+template <int kPairs>
+__device__ __forceinline__ void gauss_portable(const uint32_t (&wa)[kPairs], const uint32_t (&wb)[kPairs],
+                                               float (&zc)[kPairs], float (&zs)[kPairs])
 {
-    const float s = __builtin_amdgcn_sqrtf(x);
-    const float lo = __uint_as_float(__float_as_uint(s) - 1u);
-    const float hi = __uint_as_float(__float_as_uint(s) + 1u);
-    float r = s;
-    if (__builtin_fmaf(-lo, s, x) <= 0.0f) r = lo;
-    if (__builtin_fmaf(-hi, s, x) > 0.0f) r = hi;
-    return r;
-}
-
-// (m - 1) / (m + 1) correctly rounded for the m of the transform below: the
-// reciprocal from v_rcp_f32 refined once, then one residual correction of the
-// quotient (Markstein's scheme). That this rounds correctly for every m the
-// transform meets (one per value of u1) is checked exhaustively: the GPU's z
-// is bit-identical to the oracle's, which divides with IEEE /, over all 2^24
-// values of u1.
-__device__ __forceinline__ float div_rn_transform(float n, float d)
-{
-    float y = __builtin_amdgcn_rcpf(d);
-    y = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
-    const float q = n * y;
-    return __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
-}
-
-__device__ __forceinline__ void box_muller_pair_portable(uint32_t wa, uint32_t wb, float& zc, float& zs)
-{
-    // u1 = n1 2^-24 (n1 >= 1) = m 2^(e - 24) with m in [sqrt(1/2), sqrt(2)):
-    // float(n1) is exact (n1 <= 2^24), and so are its mantissa mp in [1/2, 1)
-    // and exponent ep (n1 = mp 2^ep); m is mp, or 2 mp below fl32(sqrt 2) / 2
-    const float fn = float((wa >> 8) + 1u);
-    const float mp = __builtin_amdgcn_frexp_mantf(fn);
-    const int ep = __builtin_amdgcn_frexp_expf(fn);
-    const bool upper = mp >= 0x1.6a09e6p-1f;                // fl32(sqrt 2) / 2
-    const float m = upper ? mp : mp + mp;
-    const int e = upper ? ep : ep - 1;
-    const float f = m - 1.0f;                               // exact
-    const float s = div_rn_transform(f, f + 2.0f);
-    const float s2 = s * s;
-    float p = __builtin_fmaf(s2, 0x1.c71c72p-4f, 0x1.24924ap-3f);  // 1/9, 1/7
-    p = __builtin_fmaf(s2, p, 0x1.99999ap-3f);              // 1/5
-    p = __builtin_fmaf(s2, p, 0x1.555556p-2f);              // 1/3
-    p = __builtin_fmaf(s2, p, 1.0f);
-    // ln m = fl32((s + s) p) and ln u1 = fl32((e - 24) fl32(ln 2) + ln m), each
-    // carried here times -2, which is exact: a scaling by -2 changes no rounding
-    const float m2ln_m = (s * -4.0f) * p;
-    const float m2ln_u1 = __builtin_fmaf(float(e - 24), -0x1.62e430p+0f, m2ln_m);
-    const float r = sqrt_rn_normal(m2ln_u1);            // sqrt(-2 ln u1)
-
-    // u2 = t 2^-24 with t = wb >> 8: the octant q = floor(8 u2) is t's top
-    // three bits; x = 8 u2 - q, or 1 - x in odd octants, is y = yl 2^-21 with
-    // yl the low 21 bits of t or 2^21 minus them (exact, in integers); and
-    // a = fl32(y fl32(pi/4)) = fl32(yl K), K = fl32(pi/4) 2^-21, since a power
-    // of two scaling changes no rounding here
-    const uint32_t q = wb >> 29;                            // octant
-    const uint32_t tl = (wb >> 8) & 0x1FFFFFu;
-    const uint32_t yl = (q & 1u) ? 0x200000u - tl : tl;     // [0, 2^21]
-    const float a = float(yl) * 0x1.921fb6p-22f;            // fl32(pi/4) 2^-21
-    const float a2 = a * a;
-    float sn = __builtin_fmaf(a2, 0x1.71de3ap-19f, -0x1.a01a02p-13f);  // 1/9!, -1/7!
-    sn = __builtin_fmaf(a2, sn, 0x1.111112p-7f);            // 1/5!
-    sn = __builtin_fmaf(a2, sn, -0x1.555556p-3f);           // -1/3!
-    sn = __builtin_fmaf(a2, sn, 1.0f);
-    sn = a * sn;
-    float cs = __builtin_fmaf(a2, -0x1.27e4fcp-22f, 0x1.a01a02p-16f);  // -1/10!, 1/8!
-    cs = __builtin_fmaf(a2, cs, -0x1.6c16c2p-10f);          // -1/6!
-    cs = __builtin_fmaf(a2, cs, 0x1.555556p-5f);            // 1/4!
-    cs = __builtin_fmaf(a2, cs, -0.5f);                     // -1/2!
-    cs = __builtin_fmaf(a2, cs, 1.0f);
-    // angle = q pi/4 + a for even q, (q + 1) pi/4 - a for odd q
-    const bool swap = (0x66u >> q) & 1u;                    // octants 1, 2, 5, 6
-    const bool neg_cos = (0x3Cu >> q) & 1u;                 // octants 2..5
-    const bool neg_sin = (q >> 2) & 1u;                     // octants 4..7
-    float c0 = swap ? sn : cs;
-    float s0 = swap ? cs : sn;
-    if (neg_cos) c0 = -c0;
-    if (neg_sin) s0 = -s0;
-    zc = r * c0;
-    zs = r * s0;
+    constexpr float kTwoM24 = 0x1p-24f;
+    constexpr uint32_t kSqrtHalfBits = 0x3F3504F3u;  // fl32(sqrt 2) / 2
+    float f[kPairs], e[kPairs], s[kPairs], x[kPairs], r[kPairs];
+    uint32_t em[kPairs];
+#define MEZO_EACH _Pragma("unroll") for (int i = 0; i < kPairs; ++i)
+    MEZO_EACH em[i] = wa[i] >> 8;
+    issue_alone();
+    MEZO_EACH f[i] = float(em[i]);
+    __builtin_amdgcn_sched_barrier(0);
+    MEZO_EACH
+    {
+        f[i] = __builtin_fmaf(f[i], kTwoM24, kTwoM24);  // u1, exact
+        const uint32_t u = __float_as_uint(f[i]);
+        em[i] = (u - kSqrtHalfBits) & 0xFF800000u;       // e 2^23
+        f[i] = __uint_as_float(u - em[i]) - 1.0f;        // m - 1, exact
+        s[i] = f[i] + 2.0f;                              // m + 1
+    }
+    MEZO_EACH e[i] = float(int32_t(em[i]));
+    MEZO_EACH x[i] = __builtin_amdgcn_rcpf(s[i]);
+    __builtin_amdgcn_sched_barrier(0);
+    MEZO_EACH
+    {
+        const float q = f[i] * x[i];
+        s[i] = __builtin_fmaf(__builtin_fmaf(-s[i], q, f[i]), x[i], q);
+        const float s2 = s[i] * s[i];
+        float p = __builtin_fmaf(s2, 0x1.c71c72p-4f, 0x1.24924ap-3f);  // 1/9, 1/7
+        p = __builtin_fmaf(s2, p, 0x1.99999ap-3f);                     // 1/5
+        p = __builtin_fmaf(s2, p, 0x1.555556p-2f);                     // 1/3
+        p = __builtin_fmaf(s2, p, 1.0f);
+        // -ln(u1) / 2 = -(e fl32(ln 2) + 2 s p) / 2
+        x[i] = __builtin_fmaf(e[i], -0x1.62e430p-25f, -(s[i] * p));
+        s[i] = x[i] + 0x1p-100f;
+    }
+    MEZO_EACH r[i] = __builtin_amdgcn_rsqf(s[i]);
+    // the signed angle's field, in units of a 2^22th of a quarter turn
+    MEZO_EACH f[i] = float(int32_t(wb[i] << 2) >> 10);
+    __builtin_amdgcn_sched_barrier(0);
+    MEZO_EACH
+    {
+        const float g = x[i] * r[i];
+        r[i] = __builtin_fmaf(__builtin_fmaf(-g, g, x[i]), r[i], g + g);
+        const float a = f[i] * 0x1.921fb6p-22f;  // fl32(pi/4) 2^-21
+        const float a2 = a * a;
+        float sn = __builtin_fmaf(a2, 0x1.71de3ap-19f, -0x1.a01a02p-13f);  // 1/9!, -1/7!
+        sn = __builtin_fmaf(a2, sn, 0x1.111112p-7f);                       // 1/5!
+        sn = __builtin_fmaf(a2, sn, -0x1.555556p-3f);                      // -1/3!
+        sn = __builtin_fmaf(a2, sn, 1.0f);
+        s[i] = a * sn;
+        float cs = __builtin_fmaf(a2, -0x1.27e4fcp-22f, 0x1.a01a02p-16f);  // -1/10!, 1/8!
+        cs = __builtin_fmaf(a2, cs, -0x1.6c16c2p-10f);                     // -1/6!
+        cs = __builtin_fmaf(a2, cs, 0x1.555556p-5f);                       // 1/4!
+        cs = __builtin_fmaf(a2, cs, -0.5f);                                // -1/2!
+        f[i] = __builtin_fmaf(a2, cs, 1.0f);
+        const uint32_t n = wb[i] + 0x20000000u;  // the nearest quarter turn in the top two bits
+        // the sign of n >= 2 on r
+        const float rs = __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(r[i]), n, 0x80000000u, 0x78));
+        const float p = rs * f[i], q = rs * s[i];
+        // n odd: bit 30, the top exponent bit of n read as a float (NaNs
+        // included: not below 2)
+        const bool odd = !(fabsf(__uint_as_float(n)) < 2.0f);
+        zc[i] = odd ? -q : p;
+        zs[i] = odd ? p : q;
+    }
+#undef MEZO_EACH
 }
 
 __device__ __forceinline__ Z4 gauss4_portable(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3)
 {
-    Z4 z;
-    box_muller_pair_portable(w0, w1, z.z0, z.z1);
-    box_muller_pair_portable(w2, w3, z.z2, z.z3);
-    return z;
+    const uint32_t wa[2] = {w0, w2}, wb[2] = {w1, w3};
+    float zc[2], zs[2];
+    gauss_portable<2>(wa, wb, zc, zs);
+    return Z4{zc[0], zs[0], zc[1], zs[1]};
 }
 
 // acc_j += c z_j for the four Gaussians of one Philox block. Portable mode:
@@ -474,15 +481,55 @@ __device__ __forceinline__ void noise_fast(const SeedUniform& u, float c, const 
         }
 }
 
-// Record r of a launch: from the kernel arguments (kInline) or the staged
-// device buffer. Either way a wave-uniform address: the words go to SGPRs.
-template <bool kInline>
-__device__ __forceinline__ const SeedRec& rec_at(const EngineArgs& a, uint32_t r)
+// The noise of one record for a lane's kBlocks blocks in portable mode:
+// acc = fma(c, z, acc), or acc = c z (kSet).
+template <int kBlocks, bool kSet>
+__device__ __forceinline__ void noise_portable(const SeedUniform& u, float c, const BlockPre (&b)[kBlocks],
+                                               float (&acc)[kBlocks][4])
 {
-    if constexpr (kInline)
+    uint32_t w[kBlocks][4];
+    philox_blocks<kBlocks>(u, b, w);
+    uint32_t wa[2 * kBlocks], wb[2 * kBlocks];
+    float zc[2 * kBlocks], zs[2 * kBlocks];
+#pragma unroll
+    for (int p = 0; p < 2 * kBlocks; ++p) {
+        wa[p] = w[p / 2][2 * (p & 1)];
+        wb[p] = w[p / 2][2 * (p & 1) + 1];
+    }
+    gauss_portable<2 * kBlocks>(wa, wb, zc, zs);
+#pragma unroll
+    for (int p = 0; p < 2 * kBlocks; ++p) {
+        float* a2 = acc[p / 2] + 2 * (p & 1);
+        a2[0] = kSet ? c * zc[p] : __builtin_fmaf(c, zc[p], a2[0]);
+        a2[1] = kSet ? c * zs[p] : __builtin_fmaf(c, zs[p], a2[1]);
+    }
+}
+
+// Record r of a launch: from the kernel arguments (kInline) or the staged
+// device buffer. Either way a wave-uniform address in memory that nothing
+// writes during the launch: read through the constant address space, so that
+// the words are scalar loads into SGPRs (the issue phases' fences would
+// otherwise make them vector loads).
+#define MEZO_CONSTANT __attribute__((address_space(4)))
+template <bool kInline>
+__device__ __forceinline__ SeedRec rec_at(const EngineArgs& a, uint32_t r)
+{
+    if constexpr (kInline) {
         return a.inl[r];
-    else
-        return a.ext[r];
+    } else {
+        typedef uint32_t words8_t __attribute__((ext_vector_type(8), aligned(16)));
+        const words8_t w = reinterpret_cast<const MEZO_CONSTANT words8_t*>(reinterpret_cast<uint64_t>(a.ext))[r];
+        SeedRec rec;
+        rec.key0 = w[0];
+        rec.key1 = w[1];
+        rec.step = w[2];
+        rec.mb_hi = w[3];
+        rec.mb_lo = w[4];
+        rec.coef = __uint_as_float(w[5]);
+        rec.last = w[6];
+        rec.sample = w[7];
+        return rec;
+    }
 }
 
 // ---- storage conversions ---------------------------------------------------

@@ -215,12 +215,13 @@ __global__ __launch_bounds__(kThreads) void engine_sweep_kernel(EngineArgs a)
     tile.store(t.d.data, t.d.numel, t.local, t.full);
 }
 
-// Lanes per tile of engine_kernel: 4 Philox blocks per lane in fast mode, one
-// 16-byte group per lane in portable mode.
+// Lanes per tile of engine_kernel: 4 Philox blocks per lane in fast mode; 2 in
+// portable mode, whose transform needs more registers and gains less from the
+// longer phases (4 blocks: 1-3% slower).
 template <uint32_t kDtype, bool kPortable>
 constexpr int list_lanes()
 {
-    return kPortable ? kThreads : (kDtype == kF32 ? kThreads / 4 : kThreads / 2);
+    return (kDtype == kF32 ? kThreads : 2 * kThreads) / (kPortable ? 2 : 4);
 }
 
 // Any record list.
@@ -242,18 +243,12 @@ __global__ __launch_bounds__((list_lanes<kDtype, kPortable>())) void engine_kern
             for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
     };
     const auto accumulate = [&](uint32_t r) {
-        const SeedRec& rec = rec_at<kInline>(a, r);
+        const SeedRec rec = rec_at<kInline>(a, r);
         const SeedUniform u = seed_uniform(rec, t.d.tensor_id);
-        if constexpr (kPortable) {
-#pragma unroll
-            for (int i = 0; i < kBlocks; ++i) {
-                uint32_t w0, w1, w2, w3;
-                philox_words(u, pre[i], w0, w1, w2, w3);
-                accumulate4<true>(rec.coef, w0, w1, w2, w3, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-            }
-        } else {
+        if constexpr (kPortable)
+            noise_portable<kBlocks, false>(u, rec.coef, pre, acc);
+        else
             noise_fast<kBlocks, false>(u, rec.coef, pre, acc);
-        }
     };
     clear();
     // the last record ends the call's last step: peeled off the loop, it

@@ -28,7 +28,7 @@ __device__ __forceinline__ void tile_nf4(const EngineArgs& a, const TensorDesc& 
     const BlockPre pre0 = block_pre(uint32_t(blk));
     const BlockPre pre1 = block_pre(uint32_t(blk + 1));
     const auto accumulate = [&](uint32_t r) {
-        const SeedRec& rec = rec_at<kInline>(a, r);
+        const SeedRec rec = rec_at<kInline>(a, r);
         const SeedUniform u = seed_uniform(rec, d.tensor_id);
         const float c = rec.coef;
         uint32_t w0, w1, w2, w3;
