@@ -119,19 +119,50 @@ __device__ __forceinline__ void philox_words(const SeedUniform& u, BlockPre b, u
 // raised wave priority, the others collect at their cheap instructions and
 // issue them in pairs: 25.0 cycles. So the loops below handle several Philox
 // blocks per lane and work in phases: issue_alone() before instructions that
-// nothing pairs with, issue_paired() before those that pair. Fences for the
-// compiler's scheduler keep the phases apart.
-__device__ __forceinline__ void issue_alone()
+// nothing pairs with, issue_paired() before those that pair. Both take the
+// values that cross the boundary as operands, so that what makes them stays
+// before it and what uses them after it (a bare fence would order neither:
+// this arithmetic has no side effects); the scheduling fences keep the rest.
+#define MEZO_SETPRIO(n)                                                                                     \
+    template <class T>                                                                                      \
+    __device__ __forceinline__ void setprio##n(T (&v)[1])                                                   \
+    {                                                                                                       \
+        asm volatile("s_setprio " #n : "+v"(v[0]));                                                         \
+    }                                                                                                       \
+    template <class T>                                                                                      \
+    __device__ __forceinline__ void setprio##n(T (&v)[2])                                                   \
+    {                                                                                                       \
+        asm volatile("s_setprio " #n : "+v"(v[0]), "+v"(v[1]));                                             \
+    }                                                                                                       \
+    template <class T>                                                                                      \
+    __device__ __forceinline__ void setprio##n(T (&v)[4])                                                   \
+    {                                                                                                       \
+        asm volatile("s_setprio " #n : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));                     \
+    }                                                                                                       \
+    template <class T>                                                                                      \
+    __device__ __forceinline__ void setprio##n(T (&v)[8])                                                   \
+    {                                                                                                       \
+        asm volatile("s_setprio " #n                                                                        \
+                     : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),  \
+                       "+v"(v[7]));                                                                         \
+    }
+MEZO_SETPRIO(0)
+MEZO_SETPRIO(1)
+#undef MEZO_SETPRIO
+
+template <class T, int kN>
+__device__ __forceinline__ void issue_alone(T (&v)[kN])
 {
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(1);
+    setprio1(v);
     __builtin_amdgcn_sched_barrier(0);
 }
 
-__device__ __forceinline__ void issue_paired()
+template <class T, int kN>
+__device__ __forceinline__ void issue_paired(T (&v)[kN])
 {
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(0);
+    setprio0(v);
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -158,39 +189,45 @@ __device__ __forceinline__ void philox_blocks(const SeedUniform& u, const BlockP
         else
             kb[r] = k1;
     }
-    uint32_t ha[kBlocks], la[kBlocks], hb[kBlocks], lb[kBlocks];
+    // y[0 .. kBlocks): the words kMulB multiplies, y[kBlocks ..): kMulA's;
+    // p: their products
+    uint32_t y1[kBlocks], y[2 * kBlocks];
+    uint64_t p1[kBlocks], p[2 * kBlocks];
     // end of round 1, and round 2 (its kMulA product is scalar)
 #pragma unroll
-    for (int i = 0; i < kBlocks; ++i) {
-        x[i][1] = b[i].hi ^ u.kx;
-        x[i][2] = (u.r2_hi ^ u.k1) ^ b[i].lo;
-    }
-    issue_alone();
+    for (int i = 0; i < kBlocks; ++i) y1[i] = b[i].hi ^ u.kx;
+    issue_alone(y1);
 #pragma unroll
-    for (int i = 0; i < kBlocks; ++i) mul_wide(kMulB, x[i][1], hb[i], lb[i]);
-    issue_paired();
+    for (int i = 0; i < kBlocks; ++i) p1[i] = uint64_t(kMulB) * y1[i];
+    issue_paired(p1);
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i) {
-        x[i][0] = hb[i] ^ (u.y1 ^ u.k0);
-        x[i][1] = lb[i];
+        y[i] = (u.r2_hi ^ u.k1) ^ b[i].lo;
+        y[kBlocks + i] = uint32_t(p1[i] >> 32) ^ (u.y1 ^ u.k0);
+        x[i][1] = uint32_t(p1[i]);
         x[i][3] = u.r2_lo;
     }
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-        issue_alone();
+        issue_alone(y);
 #pragma unroll
         for (int i = 0; i < kBlocks; ++i) {
-            mul_wide(kMulA, x[i][0], ha[i], la[i]);
-            mul_wide(kMulB, x[i][2], hb[i], lb[i]);
+            p[kBlocks + i] = uint64_t(kMulA) * y[kBlocks + i];
+            p[i] = uint64_t(kMulB) * y[i];
         }
-        issue_paired();
+        issue_paired(p);
 #pragma unroll
         for (int i = 0; i < kBlocks; ++i) {
-            x[i][0] = xor3(hb[i], x[i][1], ka[r]);
-            x[i][2] = xor3(ha[i], x[i][3], kb[r]);
-            x[i][1] = lb[i];
-            x[i][3] = la[i];
+            y[kBlocks + i] = xor3(uint32_t(p[i] >> 32), x[i][1], ka[r]);
+            y[i] = xor3(uint32_t(p[kBlocks + i] >> 32), x[i][3], kb[r]);
+            x[i][1] = uint32_t(p[i]);
+            x[i][3] = uint32_t(p[kBlocks + i]);
         }
+    }
+#pragma unroll
+    for (int i = 0; i < kBlocks; ++i) {
+        x[i][0] = y[kBlocks + i];
+        x[i][2] = y[i];
     }
 }
 
@@ -220,19 +257,6 @@ __device__ __forceinline__ void box_muller_pair_unit(uint32_t wa, uint32_t wb, f
     const float r = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
     zc = r * __builtin_amdgcn_cosf(u2);
     zs = r * __builtin_amdgcn_sinf(u2);
-}
-
-// acc_c += c z_c and acc_s += c z_s for one pair, with c the record's
-// coefficient (which carries sqrt(2 ln 2)): c r is formed once and scales
-// cos and sin inside the two fmas, so the pair costs one multiply.
-__device__ __forceinline__ void box_muller_pair_acc(uint32_t wa, uint32_t wb, float c, float& acc_c, float& acc_s)
-{
-    constexpr float kTwoM24 = 0x1p-24f;
-    const float u1 = __builtin_fmaf(float(wa >> 8), kTwoM24, kTwoM24);
-    const float u2 = float(wb >> 8) * kTwoM24;
-    const float cr = c * __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
-    acc_c = __builtin_fmaf(cr, __builtin_amdgcn_cosf(u2), acc_c);
-    acc_s = __builtin_fmaf(cr, __builtin_amdgcn_sinf(u2), acc_s);
 }
 
 __device__ __forceinline__ Z4 gauss4_unit(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3)
@@ -310,7 +334,7 @@ __device__ __forceinline__ void gauss_portable(const uint32_t (&wa)[kPairs], con
     uint32_t em[kPairs];
 #define MEZO_EACH _Pragma("unroll") for (int i = 0; i < kPairs; ++i)
     MEZO_EACH em[i] = wa[i] >> 8;
-    issue_alone();
+    issue_alone(em);
     MEZO_EACH f[i] = float(em[i]);
     __builtin_amdgcn_sched_barrier(0);
     MEZO_EACH
@@ -378,49 +402,13 @@ __device__ __forceinline__ Z4 gauss4_portable(uint32_t w0, uint32_t w1, uint32_t
     return Z4{zc[0], zs[0], zc[1], zs[1]};
 }
 
-// acc_j += c z_j for the four Gaussians of one Philox block. Portable mode:
-// the portable z, then fma(c, z, acc) as its definition states. Fast mode: c
-// carries sqrt(2 ln 2), and each pair forms c r once (box_muller_pair_acc).
-template <bool kPortable>
-__device__ __forceinline__ void accumulate4(float c, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3,
-                                            float& a0, float& a1, float& a2, float& a3)
-{
-    if constexpr (kPortable) {
-        const Z4 z = gauss4_portable(w0, w1, w2, w3);
-        a0 = __builtin_fmaf(c, z.z0, a0);
-        a1 = __builtin_fmaf(c, z.z1, a1);
-        a2 = __builtin_fmaf(c, z.z2, a2);
-        a3 = __builtin_fmaf(c, z.z3, a3);
-    } else {
-        box_muller_pair_acc(w0, w1, c, a0, a1);
-        box_muller_pair_acc(w2, w3, c, a2, a3);
-    }
-}
-
-// acc_j = c z_j for the four Gaussians of one block in fast mode (a step's
-// first record: no accumulator to clear first). The product differs from
-// fma(c, z, +0) only in the sign of a zero product, which changes theta + acc
-// only for theta = -0 (a -0 result where the accumulator's +0 gives +0).
-__device__ __forceinline__ void assign4_fast(float c, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3,
-                                             float& a0, float& a1, float& a2, float& a3)
-{
-    constexpr float kTwoM24 = 0x1p-24f;
-    const float u1a = __builtin_fmaf(float(w0 >> 8), kTwoM24, kTwoM24);
-    const float u2a = float(w1 >> 8) * kTwoM24;
-    const float cra = c * __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1a));
-    a0 = cra * __builtin_amdgcn_cosf(u2a);
-    a1 = cra * __builtin_amdgcn_sinf(u2a);
-    const float u1b = __builtin_fmaf(float(w2 >> 8), kTwoM24, kTwoM24);
-    const float u2b = float(w3 >> 8) * kTwoM24;
-    const float crb = c * __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1b));
-    a2 = crb * __builtin_amdgcn_cosf(u2b);
-    a3 = crb * __builtin_amdgcn_sinf(u2b);
-}
-
 // The noise of one record for a lane's kBlocks blocks in fast mode, in issue
-// phases: acc += c z, or acc = c z (kSet: a step's first record, see
-// assign4_fast). The same operations in the same order per element as
-// accumulate4 / assign4_fast.
+// phases: acc += c z, with c the record's coefficient (which carries
+// sqrt(2 ln 2)): per pair c r is formed once and scales cos and sin inside two
+// fmas. kSet: acc = c z (a step's first record: no accumulator to clear
+// first); the product differs from fma(c, z, +0) only in the sign of a zero
+// product, which changes theta + acc only for theta = -0 (a -0 result where
+// the accumulator's +0 gives +0).
 template <int kBlocks, bool kSet>
 __device__ __forceinline__ void noise_fast(const SeedUniform& u, float c, const BlockPre (&b)[kBlocks],
                                            float (&acc)[kBlocks][4])
@@ -428,19 +416,26 @@ __device__ __forceinline__ void noise_fast(const SeedUniform& u, float c, const 
     constexpr float kTwoM24 = 0x1p-24f;
     uint32_t x[kBlocks][4];
     philox_blocks<kBlocks>(u, b, x);
+    uint32_t ta[2 * kBlocks];  // u1's 24 bits
 #pragma unroll
-    for (int i = 0; i < kBlocks; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[i][j] >>= 8;
+    for (int i = 0; i < kBlocks; ++i) {
+        ta[2 * i] = x[i][0] >> 8;
+        ta[2 * i + 1] = x[i][2] >> 8;
+        x[i][1] >>= 8;
+        x[i][3] >>= 8;
+    }
     // from the conversions on the wave stays at the raised priority: its
     // multiplies and adds pair with another wave's conversions or xors
     // (against lowering it for them: 2% faster)
-    issue_alone();
+    issue_alone(ta);
     float f[kBlocks][4];
 #pragma unroll
-    for (int i = 0; i < kBlocks; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f[i][j] = float(x[i][j]);
+    for (int i = 0; i < kBlocks; ++i) {
+        f[i][0] = float(ta[2 * i]);
+        f[i][1] = float(x[i][1]);
+        f[i][2] = float(ta[2 * i + 1]);
+        f[i][3] = float(x[i][3]);
+    }
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i)
 #pragma unroll

@@ -22,9 +22,10 @@
 // Two kernels. Calls whose steps each hold one record (engine_sweep_kernel, at
 // most two records) are bound by memory or near it: 256 lanes per tile, one
 // 16-byte group per lane. Longer record lists (engine_kernel) are bound by
-// vector issue: 4 Philox blocks per lane (fp32: 64 lanes per tile, bf16: 128),
-// so that the instructions of 4 blocks form issue phases (engine.hpp) and the
-// key schedule's moves are spread over them: 2.54 -> 2.83e12 param-seeds/s
+// vector issue: on large sets 4 Philox blocks per lane (fp32: 64 lanes per
+// tile, bf16: 128), so that the instructions of 4 blocks form issue phases
+// (engine.hpp) and the key schedule's moves are spread over them; fewer blocks
+// on smaller sets (launch_list): 2.54 -> 2.83e12 param-seeds/s
 // (K = 64 update of the 6.7B bf16 set, 167.6 -> 150.4 ms; K = 16 of the 1.3B
 // set 8.29 -> 7.52 ms; a 6 x 8 replay of the 125M fp32 set 2.37 -> 2.16 ms)
 // against one group per lane and no phases.
@@ -201,12 +202,7 @@ __global__ __launch_bounds__(kThreads) void engine_sweep_kernel(EngineArgs a)
         const auto step = [&](const SeedRec& rec) {
             const SeedUniform u = seed_uniform(rec, t.d.tensor_id);
             float acc[Tile::kBlocks][4];
-#pragma unroll
-            for (int i = 0; i < Tile::kBlocks; ++i) {
-                uint32_t w0, w1, w2, w3;
-                philox_words(u, pre[i], w0, w1, w2, w3);
-                assign4_fast(rec.coef, w0, w1, w2, w3, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-            }
+            noise_fast<Tile::kBlocks, true>(u, rec.coef, pre, acc);
             tile.step_end(acc);
         };
         step(a.inl[0]);
@@ -215,20 +211,11 @@ __global__ __launch_bounds__(kThreads) void engine_sweep_kernel(EngineArgs a)
     tile.store(t.d.data, t.d.numel, t.local, t.full);
 }
 
-// Lanes per tile of engine_kernel: 4 Philox blocks per lane in fast mode; 2 in
-// portable mode, whose transform needs more registers and gains less from the
-// longer phases (4 blocks: 1-3% slower).
-template <uint32_t kDtype, bool kPortable>
-constexpr int list_lanes()
+// Any record list, kLanes lanes per tile.
+template <bool kInline, uint32_t kDtype, bool kPortable, int kLanes>
+__global__ __launch_bounds__(kLanes) void engine_kernel(EngineArgs a)
 {
-    return (kDtype == kF32 ? kThreads : 2 * kThreads) / (kPortable ? 2 : 4);
-}
-
-// Any record list.
-template <bool kInline, uint32_t kDtype, bool kPortable>
-__global__ __launch_bounds__((list_lanes<kDtype, kPortable>())) void engine_kernel(EngineArgs a)
-{
-    using Tile = LaneTile<kDtype, list_lanes<kDtype, kPortable>()>;
+    using Tile = LaneTile<kDtype, kLanes>;
     constexpr int kBlocks = Tile::kBlocks;
     const TileJob t = tile_job<kDtype>(a);
     Tile tile;
@@ -278,12 +265,42 @@ hipError_t launch1(void (*kernel)(EngineArgs), uint32_t tiles, int lanes, hipStr
                            stream);
 }
 
+template <bool kInline, uint32_t kDtype, bool kPortable, int kBlocks>
+hipError_t launch_blocks(const EngineArgs& args, uint32_t tiles, hipStream_t stream)
+{
+    constexpr int kLanes = int(kThreads * Layout<kDtype>::kPerGroup / 4) / kBlocks;
+    return launch1(engine_kernel<kInline, kDtype, kPortable, kLanes>, tiles, kLanes, stream, args);
+}
+
+// How many Philox blocks a lane of a list launch takes. More blocks make
+// longer issue phases, fewer make more waves, which fill the chip's 1024 SIMDs
+// evenly and hide the loads; so it goes by the tiles there are. Update times
+// against one group per lane without phases (K = 8; fp32 with 1, 2, 4 blocks):
+// 16M elements 62.6 -> 59.3, 59.3, 63.7 us; 32M 117.9 -> 112.9, 112.1, 118.5;
+// 64M 230.9 -> 220.4, 217.7, 224.6; 128M 458.6 -> 445.5, 431.7, 425.7 (K = 64
+// on 16M: 452 -> 426, 432, 453). bf16 with 2, 4: 8M 35.1 -> 33.0, 34.1; 16M
+// 62.1 -> 58.4, 58.5; 32M 116.1 -> 109.1, 107.6; 64M 224.1 -> 210.8, 205.3.
+// Portable, fp32 with 1, 2: 16M 113.2 -> 89.2, 96.7; 128M 864 -> 680, 670;
+// bf16 gains from 2 at every size (4: 4-7% slower).
+constexpr uint32_t kTilesF32For2 = 24u << 10, kTilesF32For4 = 96u << 10, kTilesBF16For4 = 8u << 10;
+constexpr uint32_t kTilesF32PortableFor2 = 64u << 10;
+
 template <bool kInline, bool kPortable>
 hipError_t launch_list(const EngineArgs& args, uint32_t dtype, uint32_t tiles, hipStream_t stream)
 {
-    if (dtype == kF32)
-        return launch1(engine_kernel<kInline, kF32, kPortable>, tiles, list_lanes<kF32, kPortable>(), stream, args);
-    return launch1(engine_kernel<kInline, kBF16, kPortable>, tiles, list_lanes<kBF16, kPortable>(), stream, args);
+    if (dtype == kF32) {
+        if constexpr (kPortable) {
+            if (tiles < kTilesF32PortableFor2) return launch_blocks<kInline, kF32, true, 1>(args, tiles, stream);
+            return launch_blocks<kInline, kF32, true, 2>(args, tiles, stream);
+        } else {
+            if (tiles < kTilesF32For2) return launch_blocks<kInline, kF32, false, 1>(args, tiles, stream);
+            if (tiles < kTilesF32For4) return launch_blocks<kInline, kF32, false, 2>(args, tiles, stream);
+            return launch_blocks<kInline, kF32, false, 4>(args, tiles, stream);
+        }
+    }
+    if constexpr (!kPortable)
+        if (tiles >= kTilesBF16For4) return launch_blocks<kInline, kBF16, false, 4>(args, tiles, stream);
+    return launch_blocks<kInline, kBF16, kPortable, 2>(args, tiles, stream);
 }
 }  // namespace
 

@@ -4,365 +4,307 @@
 // the weights are dequantized before the noise is added and quantized again
 // afterwards). Three kernels by the length of the record list: one loop over
 // any number of records (engine_nf4_kernel), two records
-// (engine_nf4_short_kernel) and one record, 16 elements per lane
-// (engine_nf4_sweep_kernel).
+// (engine_nf4_short_kernel) and one record (engine_nf4_sweep_kernel), each with
+// 16 elements per lane and 128 lanes per 2048-element tile, or 8 and 256 on
+// small sets (kDwords code dwords per lane). All three are bound by vector
+// issue (the record loop as on dense storage; around it the
+// quantizer, nf4_ops.hpp).
 #include "engine.hpp"
 #include "engine_launch.hpp"
 #include "nf4_ops.hpp"
 
 namespace mezo {
 
-// kFull: a tile wholly inside its tensor, where every lane's 8 elements exist
-// (no masks, no bounds).
-template <bool kInline, bool kPortable, bool kFull>
-__device__ __forceinline__ void tile_nf4(const EngineArgs& a, const TensorDesc& d, uint64_t e0, uint32_t packed,
-                                         float am, const NF4Lds& s)
+// The tile a workgroup handles, and a lane's share of it: its codes and the
+// absmax of their block. NF4 tensors are never shards (first = 0), so element
+// e of the tile is element e of the tensor.
+template <int kDwords>
+struct NF4Tile {
+    TensorDesc d;
+    uint64_t src_codes, src_absmax;
+    uint32_t local;
+    uint32_t valid;  // which of the lane's elements exist
+    uint32_t packed[kDwords];
+    float am;
+
+    __device__ __forceinline__ explicit NF4Tile(const EngineArgs& a)
+    {
+        const uint32_t tile = blockIdx.x;  // the grid is exactly the tiles of this table (< 2^31)
+        const uint32_t ti = a.tile_tensor[tile];
+        d = a.tensors[ti];
+        // out of place: read tensor ti of the source set (same layout), write d
+        src_codes = a.src_tensors ? a.src_tensors[ti].data : d.data;
+        src_absmax = a.src_tensors ? a.src_tensors[ti].aux : d.aux;
+        local = tile - uint32_t(d.tile_begin);
+    }
+
+    // Uniform: the tile lies wholly inside its tensor (every tile but a
+    // tensor's last). Such a tile takes paths compiled without bounds or
+    // masks, addressed as the tile's scalar base plus a 32-bit lane offset.
+    __device__ __forceinline__ bool whole() const { return local < uint32_t(d.numel / kTileNF4); }
+
+    // The tensor's Philox block of the lane's first element.
+    __device__ __forceinline__ uint32_t block() const
+    {
+        return local * uint32_t(kTileNF4 / 4) + 2u * kDwords * threadIdx.x;
+    }
+
+    template <bool kFull>
+    __device__ __forceinline__ void load()
+    {
+        if constexpr (kFull) {
+            valid = kNF4All<kDwords>;
+            const gfloat_t* ain = reinterpret_cast<const gfloat_t*>(src_absmax) + uint64_t(local) * kBlocks;
+            if constexpr (kDwords == 2) {
+                const gu32x2_t* cin = reinterpret_cast<const gu32x2_t*>(src_codes) + uint64_t(local) * kLanes;
+                const u32x2_t v = __builtin_nontemporal_load(cin + threadIdx.x);
+                packed[0] = v.x;
+                packed[1] = v.y;
+            } else {
+                const MEZO_GLOBAL uint32_t* cin =
+                    reinterpret_cast<const MEZO_GLOBAL uint32_t*>(src_codes) + uint64_t(local) * kLanes;
+                packed[0] = __builtin_nontemporal_load(cin + threadIdx.x);
+            }
+            am = ain[threadIdx.x / kBlockLanes];
+        } else {
+            const uint64_t e0 = uint64_t(local) * kTileNF4 + threadIdx.x * (8u * kDwords);
+            valid = nf4_lane_valid<kDwords>(e0, d.numel);
+#pragma unroll
+            for (int h = 0; h < kDwords; ++h) packed[h] = 0u;
+            am = 0.0f;
+            if (e0 < d.numel) {
+                const MEZO_GLOBAL uint8_t* cb = reinterpret_cast<const MEZO_GLOBAL uint8_t*>(src_codes + e0 / 2);
+#pragma unroll
+                for (uint32_t k = 0; k < 4 * kDwords; ++k)
+                    if (e0 + 2 * k < d.numel) packed[k >> 2] |= uint32_t(cb[k]) << (8 * (k & 3));
+                am = reinterpret_cast<const gfloat_t*>(src_absmax)[e0 / kNF4Block];
+            }
+        }
+    }
+
+    // The lanes of a block all store its absmax (the same value to the same
+    // address).
+    template <bool kFull>
+    __device__ __forceinline__ void store() const
+    {
+        if constexpr (kFull) {
+            gfloat_t* aout = reinterpret_cast<gfloat_t*>(d.aux) + uint64_t(local) * kBlocks;
+            if constexpr (kDwords == 2) {
+                gu32x2_t* cout = reinterpret_cast<gu32x2_t*>(d.data) + uint64_t(local) * kLanes;
+                const u32x2_t o = {packed[0], packed[1]};
+                __builtin_nontemporal_store(o, cout + threadIdx.x);
+            } else {
+                MEZO_GLOBAL uint32_t* cout =
+                    reinterpret_cast<MEZO_GLOBAL uint32_t*>(d.data) + uint64_t(local) * kLanes;
+                __builtin_nontemporal_store(packed[0], cout + threadIdx.x);
+            }
+            aout[threadIdx.x / kBlockLanes] = am;
+        } else {
+            const uint64_t e0 = uint64_t(local) * kTileNF4 + threadIdx.x * (8u * kDwords);
+            if (e0 < d.numel) {
+                MEZO_GLOBAL uint8_t* ob = reinterpret_cast<MEZO_GLOBAL uint8_t*>(d.data + e0 / 2);
+#pragma unroll
+                for (uint32_t k = 0; k < 4 * kDwords; ++k)
+                    if (e0 + 2 * k < d.numel) ob[k] = uint8_t(packed[k >> 2] >> (8 * (k & 3)));
+                reinterpret_cast<gfloat_t*>(d.aux)[e0 / kNF4Block] = am;
+            }
+        }
+    }
+
+    static constexpr uint32_t kLanes = kNF4Lanes<kDwords>, kBlocks = kTileNF4 / kNF4Block;  // per tile
+    static constexpr uint32_t kBlockLanes = kLanes / kBlocks;
+};
+
+template <int kN>
+__device__ __forceinline__ void block_pres(uint32_t blk, BlockPre (&pre)[kN])
 {
-    const uint32_t valid = kFull ? 0xFFu : nf4_valid(e0, d.numel);
-    float w[8];
-    nf4_dequant(s, packed, am, valid, w);
-    float acc[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
-    const uint64_t blk = (d.first + e0) >> 2;  // block of the logical tensor
-    const BlockPre pre0 = block_pre(uint32_t(blk));
-    const BlockPre pre1 = block_pre(uint32_t(blk + 1));
-    const auto accumulate = [&](uint32_t r) {
-        const SeedRec rec = rec_at<kInline>(a, r);
-        const SeedUniform u = seed_uniform(rec, d.tensor_id);
-        const float c = rec.coef;
-        uint32_t w0, w1, w2, w3;
-        philox_words(u, pre0, w0, w1, w2, w3);
-        accumulate4<kPortable>(c, w0, w1, w2, w3, acc[0], acc[1], acc[2], acc[3]);
-        philox_words(u, pre1, w0, w1, w2, w3);
-        accumulate4<kPortable>(c, w0, w1, w2, w3, acc[4], acc[5], acc[6], acc[7]);
-    };
-    const auto step_end = [&]() {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            w[j] = w[j] + acc[j];
-            acc[j] = 0.0f;
-        }
-        if (partial_wave(valid)) {  // only waves that reach a tensor's end
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (!((valid >> j) & 1u)) w[j] = 0.0f;
-        }
-    };
-    if (a.n_rec == 0) {  // out of place with nothing to apply: a copy
-        nf4_store<kFull>(d.data, d.aux, e0, d.numel, packed, am);
-        return;
-    }
-    // every record list ends a step with its last record, which is peeled off
-    // the loop: its quantization needs no values for a next step
-    for (uint32_t r = 0; r + 1 < a.n_rec; ++r) {
-        accumulate(r);
-        if (rec_at<kInline>(a, r).last) {
-            step_end();
-            nf4_requant<true>(s.bin, valid, w, packed, am);
-        }
-    }
-    accumulate(a.n_rec - 1);
-    step_end();
-    nf4_requant<false>(s.bin, valid, w, packed, am);
-    nf4_store<kFull>(d.data, d.aux, e0, d.numel, packed, am);
+    for (int h = 0; h < kN; ++h) pre[h] = block_pre(blk + h);
 }
 
-// The noise of record r for a lane's 8 elements: acc = c z (kSet, a step's
-// first record, which saves zeroing the accumulators; in fast mode the
-// product can differ from fma(c, z, +0) only in the sign of a zero, which no
-// code depends on, +0 and -0 sharing the zero code's bin) or acc += c z.
-template <bool kPortable, bool kSet>
-__device__ __forceinline__ void short_record(const SeedRec& rec, uint32_t tensor_id, BlockPre pre0, BlockPre pre1,
-                                             float (&acc)[8])
+// The noise of one record for a lane's kN blocks: acc = c z (kSet, a step's
+// first record, which saves zeroing the accumulators; the product can differ
+// from fma(c, z, +0) only in the sign of a zero, which no code depends on, +0
+// and -0 sharing the zero code's row) or acc += c z. The portable transform
+// takes two blocks at a time.
+template <bool kPortable, bool kSet, int kN>
+__device__ __forceinline__ void noise(const SeedRec& rec, uint32_t tensor_id, const BlockPre (&pre)[kN],
+                                      float (&acc)[kN][4])
 {
     const SeedUniform u = seed_uniform(rec, tensor_id);
     const float c = rec.coef;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        uint32_t w0, w1, w2, w3;
-        philox_words(u, h ? pre1 : pre0, w0, w1, w2, w3);
-        float* a4 = acc + 4 * h;
-        if constexpr (!kSet) {
-            accumulate4<kPortable>(c, w0, w1, w2, w3, a4[0], a4[1], a4[2], a4[3]);
-        } else if constexpr (kPortable) {
-            const Z4 z = gauss4_portable(w0, w1, w2, w3);
-            a4[0] = c * z.z0;
-            a4[1] = c * z.z1;
-            a4[2] = c * z.z2;
-            a4[3] = c * z.z3;
-        } else {
-            assign4_fast(c, w0, w1, w2, w3, a4[0], a4[1], a4[2], a4[3]);
-        }
-    }
-}
-
-// A step of one record on a lane's 8 values: w = round(w + c z). Portable
-// mode: acc = c z, then w + acc, the two roundings its definition states.
-// Fast mode: w = fma(c r, cos, w) and fma(c r, sin, w), one rounding of the
-// value plus the noise (as the oracle's step, a sum rounded once to binary32;
-// the fast mode's z is within its tolerance either way).
-template <bool kPortable>
-__device__ __forceinline__ void short_step(const SeedRec& rec, uint32_t tensor_id, BlockPre pre0, BlockPre pre1,
-                                           float (&w)[8])
-{
     if constexpr (kPortable) {
-        float acc[8];
-        short_record<true, true>(rec, tensor_id, pre0, pre1, acc);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = w[j] + acc[j];
+        for (int h = 0; h < kN; h += 2) {
+            const BlockPre p2[2] = {pre[h], pre[h + 1]};
+            float a2[2][4];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a2[j >> 2][j & 3] = acc[h + (j >> 2)][j & 3];
+            noise_portable<2, kSet>(u, c, p2, a2);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[h + (j >> 2)][j & 3] = a2[j >> 2][j & 3];
+        }
     } else {
-        const SeedUniform u = seed_uniform(rec, tensor_id);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            uint32_t w0, w1, w2, w3;
-            philox_words(u, h ? pre1 : pre0, w0, w1, w2, w3);
-            box_muller_pair_acc(w0, w1, rec.coef, w[4 * h], w[4 * h + 1]);
-            box_muller_pair_acc(w2, w3, rec.coef, w[4 * h + 2], w[4 * h + 3]);
-        }
+        noise_fast<kN, kSet>(u, c, pre, acc);
     }
 }
 
-// A lane's 8 elements (Philox blocks blk and blk + 1 of its tensor) through a
-// call of one or two records (inline): dequantize through the pair table, the
-// records, and at each step end quantize on the round-to-nearest table.
-// kFull: the 8 elements all exist (no masks).
-template <bool kPortable, bool kFull>
-__device__ __forceinline__ void short_records(const EngineArgs& a, uint32_t tensor_id, uint32_t blk, uint32_t valid,
-                                              const NF4ShortLds& s, uint32_t& packed, float& am)
+// The end of a step on a lane's elements: dequantize, add the step's noise,
+// quantize. The values are formed here and not before the noise, which keeps
+// their registers free for the record loop and lets the codes' load run beside
+// it. kFused (fast mode's steps of one record): one rounding of the value plus
+// the noise; otherwise the two that the rule states. kExact: nf4_requant_lane.
+template <bool kFused, bool kExact, bool kFull, int kDwords>
+__device__ __forceinline__ void step_end(const NF4Lds& lds, NF4Tile<kDwords>& t, const float (&acc)[2 * kDwords][4])
 {
-    float w[8];
-    nf4_dequant_pairs(s, packed, am, valid, w);
-    const BlockPre pre0 = block_pre(blk);
-    const BlockPre pre1 = block_pre(blk + 1);
-    const auto mask = [&]() {
-        if (!kFull && partial_wave(valid)) {  // only waves that reach a tensor's end
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (!((valid >> j) & 1u)) w[j] = 0.0f;
-        }
-    };
-    if (a.n_rec == 2 && !a.inl[0].last) {  // two records in one step: their sum, one rounding
-        float acc[8];
-        short_record<kPortable, true>(a.inl[0], tensor_id, pre0, pre1, acc);
-        short_record<kPortable, false>(a.inl[1], tensor_id, pre0, pre1, acc);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = w[j] + acc[j];
-    } else {  // every step of one record
-        short_step<kPortable>(a.inl[0], tensor_id, pre0, pre1, w);
-        if (a.n_rec == 2) {
-            mask();
-            nf4_requant_round<true, kPortable>(s.bin, valid, w, packed, am);
-            short_step<kPortable>(a.inl[1], tensor_id, pre0, pre1, w);
-        }
-    }
-    mask();
-    nf4_requant_round<false, kPortable>(s.bin, valid, w, packed, am);
+    float w[2 * kDwords][4];
+    nf4_lane_values<kFused>(lds, t.packed, t.am, acc, w);
+    if constexpr (!kFull) nf4_mask_lane<kDwords>(t.valid, w);
+    nf4_requant_lane<kExact, kFull>(lds, t.valid, w, t.packed, t.am);
 }
 
-// A call of two records (inline): a restore fused with the next perturbation,
-// or an update of two records, where the per-tile work around the noise weighs
-// most (one-record calls run engine_nf4_sweep_kernel). A whole tile (every
-// tile but a tensor's last) takes a path compiled without bounds or masks, its
-// codes and absmax addressed as the tile's scalar base plus a 32-bit lane
-// offset; the 8 lanes of a block all store its absmax (the same value to the
-// same address). With no records (out of place with nothing to apply) a tile
-// is copied. NF4 tensors are never shards (first = 0), so element e of the
-// tile is element e of the tensor. Compiled for 8 waves per SIMD (at most 64
-// VGPRs), the occupancy of the other kernels.
-template <bool kPortable>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kPortable ? 1 : 8, 8)))
-void engine_nf4_short_kernel(EngineArgs a)
+// A tile through a call of one record (a perturbation).
+template <bool kPortable, bool kFull, int kDwords>
+__device__ __forceinline__ void sweep_tile(const EngineArgs& a, NF4Tile<kDwords>& t, NF4Lds& lds)
 {
-    const uint32_t tile = blockIdx.x;  // the grid is exactly the tiles of this table (< 2^31)
-    const uint32_t ti = a.tile_tensor[tile];
-    const TensorDesc d = a.tensors[ti];
-    __shared__ NF4ShortLds lds;
-    // out of place: read tensor ti of the source set (same layout), write d
-    const uint64_t codes = a.src_tensors ? a.src_tensors[ti].data : d.data;
-    const uint64_t absmax = a.src_tensors ? a.src_tensors[ti].aux : d.aux;
-    const uint32_t local = tile - uint32_t(d.tile_begin);
-    const uint32_t lane = threadIdx.x;
-    if (local < uint32_t(d.numel / kTileNF4)) {  // uniform: a whole tile
-        constexpr uint32_t kWords = kTileNF4 / 8, kBlocks = kTileNF4 / kNF4Block;  // per tile
-        const MEZO_GLOBAL uint32_t* cin = reinterpret_cast<const MEZO_GLOBAL uint32_t*>(codes) + uint64_t(local) * kWords;
-        const gfloat_t* ain = reinterpret_cast<const gfloat_t*>(absmax) + uint64_t(local) * kBlocks;
-        uint32_t packed = __builtin_nontemporal_load(cin + lane);
-        float am = ain[lane >> 3];
-        nf4_short_lds_init(lds);
-        if (a.n_rec) short_records<kPortable, true>(a, d.tensor_id, local * uint32_t(kTileNF4 / 4) + 2 * lane, 0xFFu,
-                                                    lds, packed, am);
-        MEZO_GLOBAL uint32_t* cout = reinterpret_cast<MEZO_GLOBAL uint32_t*>(d.data) + uint64_t(local) * kWords;
-        gfloat_t* aout = reinterpret_cast<gfloat_t*>(d.aux) + uint64_t(local) * kBlocks;
-        __builtin_nontemporal_store(packed, cout + lane);
-        aout[lane >> 3] = am;
-    } else {
-        const uint64_t e0 = uint64_t(local) * kTileNF4 + lane * 8u;
-        uint32_t packed;
-        float am;
-        nf4_load(codes, absmax, e0, d.numel, packed, am);
-        nf4_short_lds_init(lds);
-        if (a.n_rec)
-            short_records<kPortable, false>(a, d.tensor_id, uint32_t(e0 >> 2), nf4_valid(e0, d.numel), lds, packed,
-                                            am);
-        nf4_store(d.data, d.aux, e0, d.numel, packed, am);
-    }
+    NF4LdsCopy<kDwords> copy;
+    t.template load<kFull>();
+    copy.load();
+    BlockPre pre[2 * kDwords];
+    block_pres(t.block(), pre);
+    float acc[2 * kDwords][4];
+    noise<kPortable, true>(a.inl[0], t.d.tensor_id, pre, acc);
+    copy.store(lds);
+    step_end<!kPortable, kPortable, kFull>(lds, t, acc);
+    t.template store<kFull>();
 }
 
-// Block maxima and coefficients for which the fast sweep works on w / am
-// (below): am in [2^-64, 2^64] and |c| <= 2^60, so that c / am, the values
-// v + (c / am) z and am times their maximum stay finite.
-constexpr uint32_t kFoldAmLo = 0x1F800000u;  // 2^-64
-constexpr uint32_t kFoldAmHi = 0x5F800000u;  // 2^64
-constexpr float kFoldCoefMax = 0x1p60f;
-
-// A lane's 16 elements (Philox blocks blk .. blk + 3 of its tensor) through a
-// call of one record: dequantize, add the noise (fast mode: straight into the
-// values, as short_step; portable mode: acc = c z, then w + acc), quantize.
-// Fast mode, when every lane's block maximum am and the coefficient c are in
-// range (uniform): the values are kept divided by am, v + (c / am) z with v
-// the table values themselves, and the new absmax is am times their maximum.
-// The quantizer only sees the ratio w / max |w|, so codes and absmax are those
-// of v am + c z up to a few roundings (within the fast mode's tolerance), and
-// the 16 products v am are saved. Otherwise the values are v am as in
-// portable mode.
-template <bool kPortable, bool kFull>
-__device__ __forceinline__ void sweep16(const SeedRec& rec, uint32_t tensor_id, uint32_t blk, uint32_t valid,
-                                        const NF4ShortLds& s, uint32_t (&packed)[2], float& am)
+// A call of one record (a perturbation).
+template <bool kPortable, int kDwords>
+__global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_sweep_kernel(EngineArgs a)
 {
-    float w[16];
-    float c = rec.coef;
-    float scale = 1.0f;  // the factor from the quantized values' maximum to the new absmax
-    if constexpr (kPortable) {
-        nf4_dequant_pairs16(s, packed, am, valid, w);
-    } else {
-        const bool in_range = __float_as_uint(am) - kFoldAmLo <= kFoldAmHi - kFoldAmLo;
-        if (__builtin_amdgcn_ballot_w64(!in_range) == 0 && fabsf(c) <= kFoldCoefMax) {  // uniform
-            nf4_dequant_pairs16(s, packed, 1.0f, valid, w);
-            c = c * __builtin_amdgcn_rcpf(am);
-            scale = am;
-        } else {
-            nf4_dequant_pairs16(s, packed, am, valid, w);
-        }
-    }
-    const SeedUniform u = seed_uniform(rec, tensor_id);
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        uint32_t w0, w1, w2, w3;
-        philox_words(u, block_pre(blk + h), w0, w1, w2, w3);
-        float* w4 = w + 4 * h;
-        if constexpr (kPortable) {
-            const Z4 z = gauss4_portable(w0, w1, w2, w3);
-            w4[0] = w4[0] + rec.coef * z.z0;
-            w4[1] = w4[1] + rec.coef * z.z1;
-            w4[2] = w4[2] + rec.coef * z.z2;
-            w4[3] = w4[3] + rec.coef * z.z3;
-        } else {
-            box_muller_pair_acc(w0, w1, c, w4[0], w4[1]);
-            box_muller_pair_acc(w2, w3, c, w4[2], w4[3]);
-        }
-    }
-    if (!kFull && partial_wave16(valid)) {  // only waves that reach a tensor's end
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (!((valid >> j) & 1u)) w[j] = 0.0f;
-    }
-    nf4_requant_round16<kPortable>(s.bin, valid, w, packed, am);
-    if constexpr (!kPortable) am = am * scale;
-}
-
-// A call of one record (a perturbation): 16 elements per lane, 128-lane
-// workgroups over the same 2048-element tiles (nf4_ops.hpp). Whole tiles are
-// addressed as in engine_nf4_short_kernel (codes: 8 bytes per lane; absmax
-// stored by the block's 4 lanes); the last tile of a tensor reads and writes
-// its code bytes one by one.
-template <bool kPortable>
-__global__ __launch_bounds__(kSweepLanes) __attribute__((amdgpu_waves_per_eu(8, 8)))
-void engine_nf4_sweep_kernel(EngineArgs a)
-{
-    const uint32_t tile = blockIdx.x;  // the grid is exactly the tiles of this table (< 2^31)
-    const uint32_t ti = a.tile_tensor[tile];
-    const TensorDesc d = a.tensors[ti];
-    __shared__ NF4ShortLds lds;
-    // out of place: read tensor ti of the source set (same layout), write d
-    const uint64_t codes = a.src_tensors ? a.src_tensors[ti].data : d.data;
-    const uint64_t absmax = a.src_tensors ? a.src_tensors[ti].aux : d.aux;
-    const uint32_t local = tile - uint32_t(d.tile_begin);
-    const uint32_t lane = threadIdx.x;
-    if (local < uint32_t(d.numel / kTileNF4)) {  // uniform: a whole tile
-        constexpr uint32_t kPairs = kTileNF4 / 16, kBlocks = kTileNF4 / kNF4Block;  // per tile
-        const gu32x2_t* cin = reinterpret_cast<const gu32x2_t*>(codes) + uint64_t(local) * kPairs;
-        const gfloat_t* ain = reinterpret_cast<const gfloat_t*>(absmax) + uint64_t(local) * kBlocks;
-        const u32x2_t v = __builtin_nontemporal_load(cin + lane);
-        uint32_t packed[2] = {v.x, v.y};
-        float am = ain[lane >> 2];
-        nf4_sweep_lds_init(lds);
-        sweep16<kPortable, true>(a.inl[0], d.tensor_id, local * uint32_t(kTileNF4 / 4) + 4 * lane, 0xFFFFu, lds,
-                                 packed, am);
-        gu32x2_t* cout = reinterpret_cast<gu32x2_t*>(d.data) + uint64_t(local) * kPairs;
-        gfloat_t* aout = reinterpret_cast<gfloat_t*>(d.aux) + uint64_t(local) * kBlocks;
-        const u32x2_t o = {packed[0], packed[1]};
-        __builtin_nontemporal_store(o, cout + lane);
-        aout[lane >> 2] = am;
-    } else {
-        const uint64_t e0 = uint64_t(local) * kTileNF4 + lane * 16u;
-        uint32_t packed[2] = {0u, 0u};
-        float am = 0.0f;
-        if (e0 < d.numel) {
-            const MEZO_GLOBAL uint8_t* cb = reinterpret_cast<const MEZO_GLOBAL uint8_t*>(codes + e0 / 2);
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k)
-                if (e0 + 2 * k < d.numel) packed[k >> 2] |= uint32_t(cb[k]) << (8 * (k & 3));
-            am = reinterpret_cast<const gfloat_t*>(absmax)[e0 / kNF4Block];
-        }
-        nf4_sweep_lds_init(lds);
-        sweep16<kPortable, false>(a.inl[0], d.tensor_id, uint32_t(e0 >> 2), nf4_valid16(e0, d.numel), lds, packed,
-                                  am);
-        if (e0 < d.numel) {
-            MEZO_GLOBAL uint8_t* ob = reinterpret_cast<MEZO_GLOBAL uint8_t*>(d.data + e0 / 2);
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k)
-                if (e0 + 2 * k < d.numel) ob[k] = uint8_t(packed[k >> 2] >> (8 * (k & 3)));
-            reinterpret_cast<gfloat_t*>(d.aux)[e0 / kNF4Block] = am;
-        }
-    }
-}
-
-// Record lists of more than two records: one loop over the records (tile_nf4).
-template <bool kInline, bool kPortable>
-__global__ __launch_bounds__(kThreads) void engine_nf4_kernel(EngineArgs a)
-{
-    const uint64_t tile = blockIdx.x;  // the grid is exactly the tiles of this table
-    const uint32_t ti = a.tile_tensor[tile];
-    const TensorDesc d = a.tensors[ti];
     __shared__ NF4Lds lds;
-    // out of place: read tensor ti of the source set (same layout), write d
-    const uint64_t codes = a.src_tensors ? a.src_tensors[ti].data : d.data;
-    const uint64_t absmax = a.src_tensors ? a.src_tensors[ti].aux : d.aux;
-    const uint64_t local = tile - d.tile_begin;
-    const uint64_t e0 = local * kTileNF4 + threadIdx.x * 8u;
-    uint32_t packed;
-    float am;
-    nf4_load(codes, absmax, e0, d.numel, packed, am);
-    nf4_lds_init(lds);
-    tile_nf4<kInline, kPortable, false>(a, d, e0, packed, am, lds);
+    NF4Tile<kDwords> t(a);
+    if (t.whole())
+        sweep_tile<kPortable, true>(a, t, lds);
+    else
+        sweep_tile<kPortable, false>(a, t, lds);
+}
+
+// A tile through a call of two records: a restore fused with the next
+// perturbation, or an update of two records in one step. With no records (out
+// of place with nothing to apply) the tile is copied.
+template <bool kPortable, bool kFull, int kDwords>
+__device__ __forceinline__ void short_tile(const EngineArgs& a, NF4Tile<kDwords>& t, NF4Lds& lds)
+{
+    t.template load<kFull>();
+    if (a.n_rec) {
+        NF4LdsCopy<kDwords> copy;
+        copy.load();
+        BlockPre pre[2 * kDwords];
+        block_pres(t.block(), pre);
+        float acc[2 * kDwords][4];
+        noise<kPortable, true>(a.inl[0], t.d.tensor_id, pre, acc);
+        copy.store(lds);
+        if (a.inl[0].last) {
+            step_end<!kPortable, kPortable, kFull>(lds, t, acc);
+            noise<kPortable, true>(a.inl[1], t.d.tensor_id, pre, acc);
+            step_end<!kPortable, kPortable, kFull>(lds, t, acc);
+        } else {  // two records in one step: their sum, one rounding
+            noise<kPortable, false>(a.inl[1], t.d.tensor_id, pre, acc);
+            step_end<false, kPortable, kFull>(lds, t, acc);
+        }
+    }
+    t.template store<kFull>();
+}
+
+// A call of two records (inline), or of none.
+template <bool kPortable, int kDwords>
+__global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_short_kernel(EngineArgs a)
+{
+    __shared__ NF4Lds lds;
+    NF4Tile<kDwords> t(a);
+    if (t.whole())
+        short_tile<kPortable, true>(a, t, lds);
+    else
+        short_tile<kPortable, false>(a, t, lds);
+}
+
+// Record lists of more than two records: one loop over the records. The
+// quantizer follows the rule exactly in both modes (its cost is spread over
+// the records).
+template <bool kInline, bool kPortable, int kDwords>
+__global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_kernel(EngineArgs a)
+{
+    __shared__ NF4Lds lds;
+    NF4Tile<kDwords> t(a);
+    NF4LdsCopy<kDwords> copy;
+    if (t.whole())
+        t.template load<true>();
+    else
+        t.template load<false>();
+    copy.load();
+    copy.store(lds);
+    BlockPre pre[2 * kDwords];
+    block_pres(t.block(), pre);
+    float acc[2 * kDwords][4];
+    const auto clear = [&]() {
+#pragma unroll
+        for (int j = 0; j < 8 * kDwords; ++j) acc[j >> 2][j & 3] = 0.0f;
+    };
+    clear();
+    // every record list ends a step with its last record
+    for (uint32_t r = 0; r < a.n_rec; ++r) {
+        const SeedRec rec = rec_at<kInline>(a, r);
+        noise<kPortable, false>(rec, t.d.tensor_id, pre, acc);
+        if (rec.last) {
+            step_end<false, true, false>(lds, t, acc);
+            clear();
+        }
+    }
+    if (t.whole())
+        t.template store<true>();
+    else
+        t.template store<false>();
 }
 
 namespace {
-hipError_t launch1(void (*kernel)(EngineArgs), dim3 g, dim3 b, hipStream_t stream, EngineArgs arg)
+hipError_t launch1(void (*kernel)(EngineArgs), uint32_t tiles, int lanes, hipStream_t stream, EngineArgs arg)
 {
     void* params[] = {&arg};
-    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), g, b, params, 0, stream);
+    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(tiles), dim3(uint32_t(lanes)), params, 0,
+                           stream);
 }
 
-template <bool kPortable>
-hipError_t launch_variant(const EngineArgs& args, dim3 g, dim3 b, hipStream_t stream)
+template <bool kPortable, int kDwords>
+hipError_t launch_variant(const EngineArgs& args, uint32_t tiles, hipStream_t stream)
 {
-    if (args.n_rec > kInlineRecs) return launch1(engine_nf4_kernel<false, kPortable>, g, b, stream, args);
-    if (args.n_rec == 1)
-        return launch1(engine_nf4_sweep_kernel<kPortable>, g, dim3{uint32_t(kSweepLanes)}, stream, args);
-    if (args.n_rec <= 2) return launch1(engine_nf4_short_kernel<kPortable>, g, b, stream, args);
-    return launch1(engine_nf4_kernel<true, kPortable>, g, b, stream, args);
+    constexpr int kLanes = kNF4Lanes<kDwords>;
+    if (args.n_rec > kInlineRecs)
+        return launch1(engine_nf4_kernel<false, kPortable, kDwords>, tiles, kLanes, stream, args);
+    if (args.n_rec == 1) return launch1(engine_nf4_sweep_kernel<kPortable, kDwords>, tiles, kLanes, stream, args);
+    if (args.n_rec <= 2) return launch1(engine_nf4_short_kernel<kPortable, kDwords>, tiles, kLanes, stream, args);
+    return launch1(engine_nf4_kernel<true, kPortable, kDwords>, tiles, kLanes, stream, args);
+}
+
+// Two code dwords per lane from kTilesNF4For2 tiles on, as on dense storage
+// (engine_dense.hip): fewer tiles leave too few waves. K = 8 updates with 1, 2
+// dwords, against one dword and no issue phases: 4M elements 23.2 -> 21.5, 23.4
+// us; 16M 67.5 -> 61.9, 62.5; 32M 125.9 -> 115.0, 113.9; 64M 242.9 -> 221.0,
+// 217.0; three perturbations 16M 50.5 -> 44.7, 44.4; 64M 140.1 -> 127.7, 123.8.
+// The portable transform takes two blocks at a time either way: one dword
+// (16M: 122.5 -> 85.6, 89.2; 64M 453.5 -> 315.4, 318.5; K = 64 on 128M 6741 ->
+// 4744, 4867), but for short lists on large sets (one record on 1.3B: 1440 ->
+// 1097, 1047; three on 128M 363.5 -> 266.1, 262.9).
+constexpr uint32_t kTilesNF4For2 = 12u << 10, kTilesNF4PortableFor2 = 48u << 10, kRecsNF4PortableFor2 = 4;
+
+hipError_t launch_dwords(const EngineArgs& args, bool portable, uint32_t tiles, hipStream_t stream)
+{
+    if (portable && tiles >= kTilesNF4PortableFor2 && args.n_rec <= kRecsNF4PortableFor2)
+        return launch_variant<true, 2>(args, tiles, stream);
+    if (portable) return launch_variant<true, 1>(args, tiles, stream);
+    if (tiles < kTilesNF4For2) return launch_variant<false, 1>(args, tiles, stream);
+    return launch_variant<false, 2>(args, tiles, stream);
 }
 }  // namespace
 
@@ -370,9 +312,8 @@ hipError_t launch_engine_nf4(const EngineArgs& args, bool portable, hipStream_t 
 {
     if (args.total_tiles == 0) return hipSuccess;
     if (args.total_tiles > uint64_t(0x7FFFFFFF)) return hipErrorInvalidValue;
-    const dim3 g{uint32_t(args.total_tiles)};
-    const dim3 b{uint32_t(kThreads)};
-    return portable ? launch_variant<true>(args, g, b, stream) : launch_variant<false>(args, g, b, stream);
+    const uint32_t tiles = uint32_t(args.total_tiles);
+    return launch_dwords(args, portable, tiles, stream);
 }
 
 }  // namespace mezo

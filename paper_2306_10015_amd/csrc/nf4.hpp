@@ -13,20 +13,27 @@
 // than 1/64 apart). For x in bin b, every midpoint in a lower bin is below x
 // and every midpoint in a higher bin above it, so code = (midpoints in bins
 // below b) + (x > the midpoint in bin b, if any). The tables are built at
-// compile time from the same b() the kernels evaluate. Two bin functions:
+// compile time from the same b() the kernels evaluate. Three bin functions:
 //
+// - kNF4RowTable, 129 rows, used by the engine's kernels: b(x) = (the integer
+//   nearest to 512 x + 516) / 8, whole part. One fma gives the integer as the
+//   low bits of t = fl32(512 x + kNF4RowMagic), kNF4RowMagic = 1.5 * 2^23 + 516,
+//   and t & kNF4RowMask is 8 b, the byte offset of the row. For |x| <= 1 +
+//   2^-22, b is in [0, 128] with no clamp. A row holds what the code takes in
+//   float arithmetic, whose instructions issue in pairs where compares and
+//   integer packing issue alone: code = lo + clamp(2^40 x + thr, 0, 1) with
+//   thr = -2^40 midpoint (-inf for a row without one), exact: the fma's result
+//   has the sign of x - midpoint, and no two floats here are closer than 2^-40.
 // - kNF4Table, 128 bins: b(x) = floor(fl32(64 x + 64)) clamped to [0, 127]
 //   (fma rounds 64 x + 64 once, exactly as the double expression below
-//   rounded to float does); used by the kernel that applies long record
-//   lists.
+//   rounded to float does); the rule the row table is checked against below.
 // - kNF4RoundTable, 129 bins: b(x) = the integer nearest to 64 x + 64 (ties to
 //   even), which one fma gives directly: t = fl32(64 x + kNF4BinMagic),
 //   kNF4BinMagic = 1.5 * 2^23 + 64, lies in [2^23, 2^24) where floats are 1
 //   apart, so t is 64 x + 64 rounded once to the nearest integer plus 1.5 *
 //   2^23, and the bit pattern of t is kNF4BinBase + b. For |x| <= 1 + 2^-23
 //   (every x of a block whose maximum has a normal reciprocal), b is in
-//   [0, 128] with no clamp; used by the kernel for one- and two-record calls
-//   and by the standalone quantization.
+//   [0, 128] with no clamp; used by the standalone quantization.
 #pragma once
 
 #include <stdint.h>
@@ -125,7 +132,88 @@ static_assert(kNF4RoundTable.ok, "two NF4 midpoints share a bin");
 // the extremes of a block with a normal reciprocal: |x| <= 1 + 2^-23
 static_assert(nf4_round_bin_of(-1.00000012f) == 0 && nf4_round_bin_of(1.00000012f) == kNF4RoundBins - 1,
               "bin range");
+
+// ---- the engine's row table -------------------------------------------------
+
+constexpr int kNF4Rows = 129;
+constexpr float kNF4RowMagic = 12583428.0f;  // 1.5 * 2^23 + 516
+constexpr uint32_t kNF4RowMask = 0x7F8u;     // byte offset of the row in t's bit pattern
+constexpr float kNF4Steep = 0x1p40f;
+
+struct alignas(8) NF4Row {
+    float thr;  // -2^40 midpoint, or -inf
+    float lo;   // the code below the midpoint
+};
+
+// The row of x: 512 x + 516 (exact in double for a float x) rounded to the
+// nearest integer, ties to even, over 8; clamped to [0, 128].
+constexpr int nf4_row_of(float x)
+{
+    const double t = double(x) * 512.0 + 516.0;
+    if (t <= 0.0) return 0;
+    if (t >= 1028.0) return kNF4Rows - 1;
+    const int f = static_cast<int>(t);
+    const double d = t - double(f);
+    return (d > 0.5 ? f + 1 : (d < 0.5 ? f : (f % 2 == 0 ? f : f + 1))) / 8;
+}
+
+struct NF4RowTable {
+    NF4Row row[kNF4Rows];
+    bool ok;  // no row holds two midpoints
+};
+
+constexpr NF4RowTable make_nf4_rows()
+{
+    NF4RowTable t{};
+    t.ok = true;
+    for (int b = 0; b < kNF4Rows; ++b) {
+        int lo = 0, in_row = 0;
+        t.row[b].thr = -__builtin_huge_valf();
+        for (int i = 0; i < kNF4Codes - 1; ++i) {
+            const int mb = nf4_row_of(nf4_midpoint(i));
+            if (mb < b) ++lo;
+            if (mb == b) {
+                t.row[b].thr = -kNF4Steep * nf4_midpoint(i);
+                ++in_row;
+            }
+        }
+        if (in_row > 1) t.ok = false;
+        t.row[b].lo = static_cast<float>(lo);
+    }
+    return t;
+}
+constexpr NF4RowTable kNF4RowTable = make_nf4_rows();
+static_assert(kNF4RowTable.ok, "two NF4 midpoints share a row");
+static_assert(nf4_row_of(-1.0f) == 0 && nf4_row_of(1.0f) == kNF4Rows - 1, "row range");
+
+// The code of x by either table.
+constexpr int nf4_row_code(float x)
+{
+    const NF4Row r = kNF4RowTable.row[nf4_row_of(x)];
+    return static_cast<int>(r.lo) + (double(x) * double(kNF4Steep) + double(r.thr) > 0.0 ? 1 : 0);
+}
+constexpr int nf4_bin_code(float x)
+{
+    const NF4Bin b = kNF4Table.bin[nf4_bin_of(x)];
+    return static_cast<int>(b.lo) + (x > b.mid ? 1 : 0);
+}
+// The two agree at every midpoint, on both sides of it, and at every row's edges.
+constexpr bool nf4_tables_agree()
+{
+    for (int i = 0; i < kNF4Codes - 1; ++i)
+        for (int d = -1; d <= 1; ++d) {
+            const float x = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, nf4_midpoint(i)) + uint32_t(d));
+            if (nf4_row_code(x) != nf4_bin_code(x)) return false;
+        }
+    for (int k = -1024; k <= 1024; ++k) {
+        const float x = static_cast<float>(k) / 1024.0f;
+        if (nf4_row_code(x) != nf4_bin_code(x)) return false;
+    }
+    return true;
+}
+static_assert(nf4_tables_agree(), "the row table's codes");
 static_assert(__builtin_bit_cast(uint32_t, 12582912.0f) == kNF4BinBase, "magic base");
+static_assert(kNF4RowMagic == 12582912.0f + 516.0f && (kNF4BinBase & 0x7FFu) == 0, "row magic");
 static_assert(kNF4BinMagic == 12582912.0f + 64.0f, "magic constant");
 
 }  // namespace mezo

@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void nf4_quantize_kernel(NF4ConvArgs a)
             quantize_exchange_f32(stage[threadIdx.x >> 6], c0[t], c1[t], w);
             uint32_t packed;
             float am;
-            nf4_requant_round<false>(bins, 0xFFu, w, packed, am);
+            nf4_requant_round(bins, 0xFFu, w, packed, am);
             nf4_store<true>(a.codes, a.absmax, (t0 + t) * kTileNF4 + lane_e, a.n, packed, am);
         }
     } else if ((t0 + kQuantTiles) * kTileNF4 <= a.n) {  // uniform: whole bf16 tiles
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kThreads) void nf4_quantize_kernel(NF4ConvArgs a)
         for (uint32_t t = 0; t < kQuantTiles; ++t) {
             uint32_t packed;
             float am;
-            nf4_requant_round<false>(bins, 0xFFu, w[t], packed, am);
+            nf4_requant_round(bins, 0xFFu, w[t], packed, am);
             nf4_store<true>(a.codes, a.absmax, (t0 + t) * kTileNF4 + lane_e, a.n, packed, am);
         }
     } else {
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(kThreads) void nf4_quantize_kernel(NF4ConvArgs a)
             nf4_quantize_load<false>(a, e0, valid, w);
             uint32_t packed;
             float am;
-            nf4_requant_round<false>(bins, valid, w, packed, am);
+            nf4_requant_round(bins, valid, w, packed, am);
             nf4_store(a.codes, a.absmax, e0, a.n, packed, am);
         }
     }

@@ -1,0 +1,85 @@
+// nf4_row_check.cpp — TEST INFRASTRUCTURE ONLY: the row table of nf4.hpp and
+// the lookup arithmetic of the NF4 engine kernels (nf4_ops.hpp) replayed on
+// the host over every float x with 2^-10 <= |x| <= 1 + 2^-22, and the general
+// lookup over special values too. Each code is compared with the number of
+// midpoints strictly below x (read from stdin as in nf4_table_check.cpp).
+#include <cmath>
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+
+#include "nf4.hpp"
+
+static uint32_t bits(float x)
+{
+    uint32_t u;
+    std::memcpy(&u, &x, 4);
+    return u;
+}
+
+static float from_bits(uint32_t u)
+{
+    float x;
+    std::memcpy(&x, &u, 4);
+    return x;
+}
+
+using mezo::kNF4RowMagic;
+using mezo::kNF4RowMask;
+using mezo::kNF4Rows;
+using mezo::kNF4Steep;
+
+static uint32_t code_usual(float x)
+{
+    const uint32_t off = bits(std::fmaf(x, 512.0f, kNF4RowMagic)) & kNF4RowMask;
+    if (off / 8 >= uint32_t(kNF4Rows)) return 99;  // past the table
+    const mezo::NF4Row& e = mezo::kNF4RowTable.row[off / 8];
+    const float up = std::fmin(std::fmax(std::fmaf(x, kNF4Steep, e.thr), 0.0f), 1.0f);
+    // the gathered code of four equal elements: exact, in the low 16 bits
+    float g = 128.0f;
+    for (int j = 0; j < 4; ++j) g = std::fmaf(g, 16.0f, e.lo) + up;
+    const uint32_t p = bits(g) & 0xFFFFu;
+    return p == (p & 15u) * 0x1111u ? (p & 15u) : 99u;
+}
+
+static uint32_t code_general(float x)
+{
+    const float xs = x == x ? x : -2.0f;
+    const int k = int(bits(std::fmaf(xs, 512.0f, kNF4RowMagic))) - int(mezo::kNF4BinBase);
+    const uint32_t off = uint32_t(k < 0 ? 0 : (k > 1028 ? 1028 : k)) & kNF4RowMask;
+    const mezo::NF4Row& e = mezo::kNF4RowTable.row[off / 8];
+    return uint32_t(e.lo) + (std::fmaf(x, kNF4Steep, e.thr) > 0.0f ? 1u : 0u);
+}
+
+int main()
+{
+    float mid[15];
+    for (int i = 0; i < 15; ++i) {
+        unsigned u;
+        if (std::scanf("%x", &u) != 1) return 2;
+        mid[i] = from_bits(u);
+    }
+    const auto want = [&](float x) {
+        uint32_t c = 0;
+        for (int i = 0; i < 15; ++i) c += mid[i] < x ? 1u : 0u;
+        return c;
+    };
+    unsigned long long bad = 0, n = 0;
+    for (uint32_t s = 0; s < 2; ++s)
+        for (uint32_t m = bits(0x1p-10f); m <= bits(1.0f) + 2; ++m, ++n) {
+            const float x = from_bits(m | (s << 31));
+            const uint32_t w = want(x);
+            bad += code_usual(x) != w;
+            bad += code_general(x) != w;
+        }
+    const float special[] = {0.0f,   -0.0f, 1e-30f, -1e-30f, 1e-45f, INFINITY, -INFINITY, NAN,
+                             3.4e38f, -3.4e38f, 2.0f, -2.0f, 1e6f, -1e6f};
+    for (float x : special) {
+        const uint32_t w = x == x ? want(x) : 0u;  // NaN: no midpoint is below it
+        bad += code_general(x) != w;
+        if (std::fabs(x) <= 1.0f) bad += code_usual(x) != w;
+        ++n;
+    }
+    std::printf("%llu values, %llu mismatches\n", n, bad);
+    return bad ? 1 : 0;
+}

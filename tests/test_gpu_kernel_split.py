@@ -101,3 +101,57 @@ def test_list_kernel_against_the_oracle(mz, orc, dtype, K):
         assert np.array_equal(to_host(pads[i][len(h):]), np.full(16, 1, dtype=h.dtype)), len(h)
     ps.close()
     pd.close()
+
+
+@pytest.mark.parametrize("dtype,tiles,gaussian", [
+    # one set on each side of the sizes at which a lane takes more blocks
+    (synth.F32, 24 * 1024, "fast"), (synth.F32, 96 * 1024, "fast"), (synth.BF16, 8 * 1024, "fast"),
+    (synth.F32, 64 * 1024, "portable"), (synth.NF4, 12 * 1024, "fast"), (synth.NF4, 48 * 1024, "portable")])
+def test_list_kernels_of_large_sets(mz, dtype, tiles, gaussian):
+    """Ragged tensors beside a large one that makes the set's tile count cross
+    the line: three records in one pass against three calls."""
+    import torch
+    g = mz.GAUSS_PORTABLE if gaussian == "portable" else mz.GAUSS_FAST
+    per = 1024 if dtype == synth.F32 else 2048
+    small_tiles = sum((n + per - 1) // per for n in SIZES)
+    seeds, scales = records(3, 23)
+    for big_tiles in (tiles - small_tiles - 1, tiles - small_tiles):
+        sizes = SIZES + [big_tiles * per - 5]
+        ids = [3 * i + 2 for i in range(len(sizes))]
+
+        def fresh():
+            gen = torch.Generator(device="cuda")
+            gen.manual_seed(5)
+            out = []
+            for n in sizes:
+                if dtype == synth.NF4:
+                    t = mz.NF4Tensor.empty(n)
+                    t.codes.random_(0, 256, generator=gen)
+                    if n % 2:
+                        t.codes[-1] &= 15
+                    t.absmax.uniform_(0.04, 0.06, generator=gen)
+                    out.append(t)
+                else:
+                    x = torch.empty(n, device="cuda").normal_(0.0, 0.02, generator=gen)
+                    out.append(x if dtype == synth.F32 else x.bfloat16())
+            return out
+
+        a, b = fresh(), fresh()
+        pa, pb = mz.ParamSet(a, ids, gaussian=g), mz.ParamSet(b, ids, gaussian=g)
+        pa.perturb_multi(seeds, scales)
+        for s, c in zip(seeds, scales):
+            pb.perturb(s, c)
+        for n, x, y in zip(sizes, a, b):
+            if dtype != synth.NF4:
+                same = torch.int32 if dtype == synth.F32 else torch.int16
+                assert torch.equal(x.view(same), y.view(same)), (big_tiles, n)
+            elif gaussian == "portable":
+                assert torch.equal(x.codes, y.codes) and torch.equal(x.absmax, y.absmax), (big_tiles, n)
+            else:
+                # one-record calls may round the quantizer differently: a code
+                # here and there, never more
+                d = (mz.nf4_dequantize(x) - mz.nf4_dequantize(y)).abs() > 1e-4
+                assert float(d.float().mean()) <= max(2.0 / min(n, 64), 0.0) if n < 4096 else float(
+                    d.float().mean()) <= 1e-4, (big_tiles, n)
+        pa.close()
+        pb.close()
