@@ -72,42 +72,67 @@ __device__ __forceinline__ uint64_t mix_whole_tile(u32x4_t v, uint64_t cpos_tile
     return fmix64(lo ^ p0 ^ tmix) + fmix64(hi ^ (p0 + kChunkPos) ^ tmix);
 }
 
-// A lane's share of a tensor's last tile, which the tensor's end may cut:
-// only the elements that exist, the last chunk zero-padded.
+// The bytes of a lane's 16 at addr that exist (fewer than 16), the rest zero.
 template <uint32_t kDtype>
-__device__ __forceinline__ uint64_t mix_last_tile(const TensorDesc& d, uint64_t local)
+__device__ __forceinline__ u32x4_t load_ragged(uint64_t addr, uint32_t bytes)
 {
-    constexpr uint64_t kPer = Layout<kDtype>::kPerGroup;
-    constexpr uint64_t kEsz = 16 / kPer;
-    const uint64_t nchunks = (d.numel * kEsz + 7) / 8;
-    const uint64_t cbase = d.first * kEsz / 8;  // chunk number of the shard's first byte
-    const uint64_t tmix = uint64_t(d.tensor_id) * kChunkTensor;
-    const uint64_t grp = group_index<1>(local, 0);
-    const uint64_t c0 = grp * 2;  // the group's first chunk within the shard
-    if (c0 >= nchunks) return 0;
-    uint4 v;
-    if ((grp + 1) * kPer <= d.numel) {
-        v = load_stream(d.data + grp * 16);
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    if constexpr (kDtype == kF32) {
+        const MEZO_GLOBAL uint32_t* in = reinterpret_cast<const MEZO_GLOBAL uint32_t*>(addr);
+#pragma unroll
+        for (uint32_t j = 0; j < 3; ++j)
+            if (4 * j < bytes) w[j] = in[j];
     } else {
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        if constexpr (kDtype == kF32) {
-            const MEZO_GLOBAL uint32_t* in = reinterpret_cast<const MEZO_GLOBAL uint32_t*>(d.data);
+        const gu16_t* in = reinterpret_cast<const gu16_t*>(addr);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (grp * 4 + j < d.numel) w[j] = in[grp * 4 + j];
-        } else {
-            const gu16_t* in = reinterpret_cast<const gu16_t*>(d.data);
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (grp * 8 + j < d.numel) w[j >> 1] |= uint32_t(in[grp * 8 + j]) << (16 * (j & 1));
-        }
-        v = make_uint4(w[0], w[1], w[2], w[3]);
+        for (uint32_t j = 0; j < 7; ++j)
+            if (2 * j < bytes) w[j >> 1] |= uint32_t(in[j]) << (16 * (j & 1));
     }
-    const uint64_t lo = uint64_t(v.x) | (uint64_t(v.y) << 32);
-    const uint64_t hi = uint64_t(v.z) | (uint64_t(v.w) << 32);
-    uint64_t s = fmix64(lo ^ ((cbase + c0) * kChunkPos) ^ tmix);
-    if (c0 + 1 < nchunks) s += fmix64(hi ^ ((cbase + c0 + 1) * kChunkPos) ^ tmix);
-    return s;
+    return u32x4_t{w[0], w[1], w[2], w[3]};
+}
+
+// The mixes of a lane's chunks of tiles t .. t + n - 1 (1 <= n <= kTiles) of
+// any tensors, each whole or cut by its tensor's end: the map entries of all
+// of them are read first, then their descriptors, then the data, so that the
+// group waits for three latencies however many tensors it crosses.
+template <uint32_t kDtype, uint32_t kTiles>
+__device__ __forceinline__ uint64_t mix_any_tiles(const ChecksumArgs& a, uint64_t t, uint32_t n, uint64_t cpos_lane)
+{
+    constexpr uint64_t kEsz = 16 / Layout<kDtype>::kPerGroup;
+    constexpr uint64_t kTileBytes = uint64_t(kThreads) * 16;
+    uint32_t ti[kTiles], bytes[kTiles];  // bytes: of the tile that exist
+    uint64_t addr[kTiles], cpos[kTiles], tmix[kTiles];
+#pragma unroll
+    for (uint32_t j = 0; j < kTiles; ++j) ti[j] = a.tile_tensor[t + (j < n ? j : n - 1)];
+#pragma unroll
+    for (uint32_t j = 0; j < kTiles; ++j) {
+        const TensorDesc& d = a.tensors[ti[j]];
+        const uint64_t local = t + (j < n ? j : n - 1) - d.tile_begin;
+        const uint64_t left = d.numel * kEsz - local * kTileBytes;
+        bytes[j] = j < n ? uint32_t(left < kTileBytes ? left : kTileBytes) : 0u;
+        addr[j] = d.data + local * kTileBytes;
+        cpos[j] = (d.first * kEsz / 8 + 2 * local * kThreads) * kChunkPos;
+        tmix[j] = uint64_t(d.tensor_id) * kChunkTensor;
+    }
+    const uint32_t off = threadIdx.x * 16u;
+    u32x4_t v[kTiles];
+#pragma unroll
+    for (uint32_t j = 0; j < kTiles; ++j) {
+        v[j] = u32x4_t{0u, 0u, 0u, 0u};
+        if (off + 16 <= bytes[j])
+            v[j] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4_t*>(addr[j]) + threadIdx.x);
+    }
+    uint64_t sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kTiles; ++j) {
+        if (off < bytes[j] && off + 16 > bytes[j]) v[j] = load_ragged<kDtype>(addr[j] + off, bytes[j] - off);
+        const uint64_t p0 = cpos[j] + cpos_lane;
+        const uint64_t lo = uint64_t(v[j].x) | (uint64_t(v[j].y) << 32);
+        const uint64_t hi = uint64_t(v[j].z) | (uint64_t(v[j].w) << 32);
+        if (off < bytes[j]) sum += fmix64(lo ^ p0 ^ tmix[j]);
+        if (off + 8 < bytes[j]) sum += fmix64(hi ^ (p0 + kChunkPos) ^ tmix[j]);
+    }
+    return sum;
 }
 
 // The tensor a run of tiles is in: its descriptor's fields in scalar
@@ -168,41 +193,23 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
         RunCursor<kTileElems> c;
         c.tensors = a.tensors;
         c.load(a.tile_tensor[t0]);
-        // the chunk-position term of tile `local` of the cursor's tensor
-        const auto cpos_of = [&](uint64_t local) { return (c.first * kEsz / 8 + 2 * local * kThreads) * kChunkPos; };
-        const auto one_tile = [&](uint64_t tile) {
-            c.seek(tile);
-            const uint64_t local = tile - c.begin;
-            if ((local + 1) * kTileElems <= c.numel) {  // uniform: all but a tensor's last tile
-                const u32x4_t v = load_whole_tile(c.data, local);
-                sum += mix_whole_tile(v, cpos_of(local), uint64_t(c.id) * kChunkTensor, cpos_lane);
-            } else {
-                TensorDesc d;
-                d.data = c.data;
-                d.numel = c.numel;
-                d.first = c.first;
-                d.tensor_id = c.id;
-                sum += mix_last_tile<kDtype>(d, local);
-            }
-        };
-        uint64_t t = t0;
-        for (; t + kInFlight <= t_end; t += kInFlight) {
-            c.seek(t);
+        for (uint64_t t = t0; t < t_end; t += kInFlight) {
+            if (t >= c.end) c.load(a.tile_tensor[t]);
             const uint64_t local = t - c.begin;
-            if ((local + kInFlight) * kTileElems <= c.numel) {  // uniform: all kInFlight tiles whole, one tensor
+            if (t + kInFlight <= t_end && (local + kInFlight) * kTileElems <= c.numel) {  // uniform
                 u32x4_t v[kInFlight];
 #pragma unroll
                 for (uint64_t j = 0; j < kInFlight; ++j) v[j] = load_whole_tile(c.data, local + j);
-                const uint64_t cpos = cpos_of(local);
+                const uint64_t cpos = (c.first * kEsz / 8 + 2 * local * kThreads) * kChunkPos;
                 const uint64_t tmix = uint64_t(c.id) * kChunkTensor;
 #pragma unroll
                 for (uint64_t j = 0; j < kInFlight; ++j)
                     sum += mix_whole_tile(v[j], cpos + j * (2 * kThreads * kChunkPos), tmix, cpos_lane);
             } else {
-                for (uint64_t j = 0; j < kInFlight; ++j) one_tile(t + j);
+                const uint64_t n = t_end - t < kInFlight ? t_end - t : kInFlight;
+                sum += mix_any_tiles<kDtype, uint32_t(kInFlight)>(a, t, uint32_t(n), cpos_lane);
             }
         }
-        for (; t < t_end; ++t) one_tile(t);
     }
     add_workgroup_sum(sum, a);
 }

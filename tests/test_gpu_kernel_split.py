@@ -155,3 +155,30 @@ def test_list_kernels_of_large_sets(mz, dtype, tiles, gaussian):
                     d.float().mean()) <= 1e-4, (big_tiles, n)
         pa.close()
         pb.close()
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("spread", [1, 11])
+def test_checksum_runs_across_tensor_ends(mz, orc, dtype, spread):
+    """A workgroup's run of tiles in groups of eight: short tensors one after
+    another, in one group or several, between tensors of many tiles, runs that
+    are no multiple of eight, and a shard's chunk numbers."""
+    per = 1024 if dtype == synth.F32 else 2048
+    sizes = list(SIZES)
+    for i in range(spread):
+        sizes += [(37 * i + 300) * per + [0, 1, 5, per - 1][i % 4], 3, per + 2, 9, 2 * per, per - 3]
+    hs = [synth.theta0_tensor((n,), dtype, i, 9) for i, n in enumerate(sizes)]
+    ids = [4 * i + 3 for i in range(len(sizes))]
+    want = orc.checksum(hs, ids)
+    devs = [to_device(h) for h in hs]
+    ps = mz.ParamSet(devs, ids)
+    assert ps.checksum() == want and ps.checksum() == want
+    ps.close()
+    # every tensor's rest after its first 16 elements, or all of a short one
+    cuts = [16 if n > 16 else 0 for n in sizes]
+    heads = [(d[:16], i) for d, i, c in zip(devs, ids, cuts) if c]
+    a = mz.ParamSet([d for d, _ in heads], [i for _, i in heads])
+    b = mz.ParamSet([to_device(h[c:]) for h, c in zip(hs, cuts)], ids, firsts=cuts)
+    assert (a.checksum() + b.checksum()) & 0xFFFFFFFFFFFFFFFF == want
+    a.close()
+    b.close()
