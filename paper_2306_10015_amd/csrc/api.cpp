@@ -209,8 +209,8 @@ struct mezo_paramset {
     std::atomic<uint32_t> gaussian{MEZO_GAUSS_FAST};
     mezo::TensorDesc* d_table[kTypes] = {};
     uint32_t* d_tile_tensor[kTypes] = {};  // tensor index of every tile
-    // One event per stream the paramset's kernels ran on, recorded after the
-    // latest launch on that stream: destroy waits for all of them before it
+    // One event per stream the paramset's kernels ran on, completed by the
+    // latest launch on that stream itself: destroy waits for all of them before it
     // frees the tables (work on an earlier stream may still be running). At
     // most kUses streams are tracked; a further stream takes over the entry
     // used longest ago, after waiting on the host for that entry's event. The
@@ -348,20 +348,20 @@ int use_entry(mezo_paramset* ps, hipStream_t stream, mezo_paramset::Use*& out)
     return MEZO_OK;
 }
 
-// Record that ps's tables are read by work enqueued so far on stream, in its
-// use entry (after ensure_device: the events exist; nothing is created here).
-int record_use(mezo_paramset* ps, mezo_paramset::Use* use, hipStream_t stream)
-{
-    use->seq = ++ps->use_seq;
-    MEZO_HIP(hipEventRecord(use->done, stream));
-    return MEZO_OK;
-}
+// That ps's tables are read by the work just enqueued on the entry's stream,
+// whose last launch completes the entry's event.
+void mark_use(mezo_paramset* ps, mezo_paramset::Use* use) { use->seq = ++ps->use_seq; }
 
-int mark_use(mezo_paramset* ps, hipStream_t stream)
+// The same for a source set, whose event is recorded after the launch (the
+// launch itself completes its destination's).
+int record_use(mezo_paramset* ps, hipStream_t stream)
 {
     mezo_paramset::Use* use = nullptr;
     const int rc = use_entry(ps, stream, use);
-    return rc ? rc : record_use(ps, use, stream);
+    if (rc) return rc;
+    mark_use(ps, use);
+    MEZO_HIP(hipEventRecord(use->done, stream));
+    return MEZO_OK;
 }
 
 // Records one engine launch applies at most when a call can split its list
@@ -377,11 +377,15 @@ struct RecSpan {
 };
 
 // One engine launch per storage type of ps with the records args carries
-// (src: read that set, of the same layout, and write ps).
+// (src: read that set, of the same layout, and write ps). The last of them
+// completes use's event (use: the stream's entry; null under capture).
 hipError_t launch_tables(const mezo_paramset* ps, mezo::EngineArgs& args, bool portable, hipStream_t stream,
-                         const mezo_paramset* src)
+                         const mezo_paramset* src, const mezo_paramset::Use* use)
 {
     hipError_t e = hipSuccess;
+    uint32_t last = 0;
+    for (uint32_t dt = 0; dt < mezo::kStorageTypes; ++dt)
+        if (!ps->table[dt].empty()) last = dt;
     for (uint32_t dt = 0; dt < mezo::kStorageTypes && e == hipSuccess; ++dt) {
         if (ps->table[dt].empty()) continue;
         args.tensors = ps->d_table[dt];
@@ -389,6 +393,7 @@ hipError_t launch_tables(const mezo_paramset* ps, mezo::EngineArgs& args, bool p
         args.src_tensors = src ? src->d_table[dt] : nullptr;
         args.n_tensors = static_cast<uint32_t>(ps->table[dt].size());
         args.total_tiles = ps->total_tiles[dt];
+        args.done = use && dt == last ? use->done : nullptr;
         e = dt == mezo::kNF4 ? mezo::launch_engine_nf4(args, portable, stream)
                              : mezo::launch_engine_dense(args, dt, portable, stream);
     }
@@ -427,6 +432,11 @@ int launch_records(mezo_paramset* ps, RecSpan recs, bool portable, hipStream_t s
             return MEZO_EINVAL;
         }
     }
+    mezo_paramset::Use* use = nullptr;  // a graph's launches are the caller's to wait for
+    if (!capture) {
+        rc = use_entry(ps, stream, use);
+        if (rc) return rc;
+    }
     mezo::EngineArgs args;
     std::memset(&args, 0, sizeof(args));
     args.n_rec = static_cast<uint32_t>(recs.size);
@@ -455,7 +465,7 @@ int launch_records(mezo_paramset* ps, RecSpan recs, bool portable, hipStream_t s
                                 hipMemcpyHostToDevice, stream));
         args.ext = slot->dev;
     }
-    hipError_t e = launch_tables(ps, args, portable, stream, src);
+    hipError_t e = launch_tables(ps, args, portable, stream, src, use);
     // The slot is reused only after this event: recorded whenever its copy
     // was enqueued, also when a launch failed.
     if (slot) {
@@ -463,10 +473,9 @@ int launch_records(mezo_paramset* ps, RecSpan recs, bool portable, hipStream_t s
         if (e == hipSuccess) e = er;
     }
     if (e != hipSuccess) return hip_fail(e, "engine launch");
-    if (capture) return MEZO_OK;  // a graph's launches are the caller's to wait for
-    rc = mark_use(ps, stream);
-    if (rc == MEZO_OK && src && src != ps) rc = mark_use(src, stream);
-    return rc;
+    if (capture) return MEZO_OK;
+    mark_use(ps, use);
+    return src && src != ps ? record_use(src, stream) : MEZO_OK;
 }
 
 int launch_records(mezo_paramset* ps, const std::vector<mezo::SeedRec>& recs, bool portable, hipStream_t stream,
@@ -826,9 +835,15 @@ int mezo_replay_noalloc(mezo_paramset_t ps, const mezo_step_t* steps, uint32_t T
             if (e != hipSuccess) return hip_fail(e, "record staging");
             args.ext = scratch;
         }
-        const hipError_t e = launch_tables(ps, args, portable, st, nullptr);
+        mezo_paramset::Use* use = nullptr;
+        if (!capture) {
+            rc = use_entry(ps, st, use);
+            if (rc) return rc;
+        }
+        const hipError_t e = launch_tables(ps, args, portable, st, nullptr, use);
         if (e != hipSuccess) return hip_fail(e, "engine launch");
-        return capture ? MEZO_OK : mark_use(ps, st);
+        if (use) mark_use(ps, use);
+        return MEZO_OK;
     });
 }
 
@@ -862,10 +877,12 @@ int mezo_checksum(mezo_paramset_t ps, uint64_t* out_dev, void* stream)
             rc = use_entry(ps, st, use);
             if (rc) return rc;
             pair = static_cast<size_t>(use - ps->uses);
+            for (int i = 0; i < n; ++i) tabs[i].done = use->done;
         }
         MEZO_HIP(mezo::launch_checksum(tabs, dts, n, reinterpret_cast<unsigned long long*>(out_dev),
                                        ps->d_ck + 2 * pair, ps->device, st));
-        return capture ? MEZO_OK : record_use(ps, use, st);
+        if (use) mark_use(ps, use);
+        return MEZO_OK;
     });
 }
 

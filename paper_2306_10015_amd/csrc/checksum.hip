@@ -7,6 +7,7 @@
 #include <atomic>
 
 #include "checksum_launch.hpp"
+#include "launch.hpp"
 #include "stream_io.hpp"
 #include "tiles.hpp"
 
@@ -358,12 +359,6 @@ namespace {
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_cus[kMaxDevices];  // compute units per device, 0 = not yet asked
 
-template <class Arg>
-hipError_t launch1(void (*kernel)(Arg), dim3 g, dim3 b, hipStream_t stream, Arg arg)
-{
-    void* params[] = {&arg};
-    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), g, b, params, 0, stream);
-}
 }  // namespace
 
 hipError_t launch_checksum(const ChecksumArgs* tables, const uint32_t* dtypes, int n_tables,
@@ -380,7 +375,7 @@ hipError_t launch_checksum(const ChecksumArgs* tables, const uint32_t* dtypes, i
     for (int i = 0; i < n_tables; ++i)
         if (tables[i].total_tiles) last = i;
     // no tiles at all (the C ABI never passes such a set): the checksum is 0
-    if (last < 0) return launch1(zero_u64_kernel, dim3(1), dim3(64), stream, out);
+    if (last < 0) return launch1(zero_u64_kernel, 1, 64, stream, out, nullptr);
     hipError_t e = hipSuccess;
     for (int i = 0; i <= last; ++i) {
         if (tables[i].total_tiles == 0) continue;
@@ -396,14 +391,14 @@ hipError_t launch_checksum(const ChecksumArgs* tables, const uint32_t* dtypes, i
         const uint64_t need = (tables[i].total_tiles + per_wg - 1) / per_wg;
         const uint64_t cap = uint64_t(cus) * (dtypes[i] == kNF4 ? 4 : 2);
         const uint64_t grid = need < cap ? need : cap;
-        const dim3 g{uint32_t(grid)};
-        const dim3 b{uint32_t(kThreads)};
+        const uint32_t g = uint32_t(grid);
+        const hipEvent_t done = i == last ? args.done : nullptr;
         if (dtypes[i] == kF32)
-            e = launch1(checksum_kernel<kF32>, g, b, stream, args);
+            e = launch1(checksum_kernel<kF32>, g, kThreads, stream, args, done);
         else if (dtypes[i] == kBF16)
-            e = launch1(checksum_kernel<kBF16>, g, b, stream, args);
+            e = launch1(checksum_kernel<kBF16>, g, kThreads, stream, args, done);
         else
-            e = launch1(checksum_nf4_kernel, g, b, stream, args);
+            e = launch1(checksum_nf4_kernel, g, kThreads, stream, args, done);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

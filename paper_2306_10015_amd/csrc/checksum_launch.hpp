@@ -17,6 +17,7 @@ struct ChecksumArgs {
     // device, two words that are zero between calls: [0] the running sum
     // (64-bit atomic adds), [1] the workgroups of this launch done so far
     unsigned long long* acc;
+    hipEvent_t done;  // host only: completed by the call's last launch, or null
     uint32_t last;  // 1: this launch ends the call (writes *out, clears acc[0])
 };
 

@@ -31,6 +31,7 @@
 // against one group per lane and no phases.
 #include "engine.hpp"
 #include "engine_launch.hpp"
+#include "launch.hpp"
 #include "stream_io.hpp"
 #include "tiles.hpp"
 
@@ -255,21 +256,11 @@ __global__ __launch_bounds__(kLanes) void engine_kernel(EngineArgs a)
 }
 
 namespace {
-// Launch a one-argument kernel and return the status of this launch itself
-// (not the thread's last HIP error, which may hold an earlier failure of
-// another caller's call).
-hipError_t launch1(void (*kernel)(EngineArgs), uint32_t tiles, int lanes, hipStream_t stream, EngineArgs arg)
-{
-    void* params[] = {&arg};
-    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(tiles), dim3(uint32_t(lanes)), params, 0,
-                           stream);
-}
-
 template <bool kInline, uint32_t kDtype, bool kPortable, int kBlocks>
 hipError_t launch_blocks(const EngineArgs& args, uint32_t tiles, hipStream_t stream)
 {
     constexpr int kLanes = int(kThreads * Layout<kDtype>::kPerGroup / 4) / kBlocks;
-    return launch1(engine_kernel<kInline, kDtype, kPortable, kLanes>, tiles, kLanes, stream, args);
+    return launch1(engine_kernel<kInline, kDtype, kPortable, kLanes>, tiles, kLanes, stream, args, args.done);
 }
 
 // How many Philox blocks a lane of a list launch takes. More blocks make
@@ -312,8 +303,8 @@ hipError_t launch_engine_dense(const EngineArgs& args, uint32_t dtype, bool port
     // at most two records, each a step of its own (or none): the sweep kernel
     const bool sweep = args.n_rec <= 1 || (args.n_rec == 2 && args.inl[0].last);
     if (sweep && (!portable || args.n_rec == 0)) {
-        if (dtype == kF32) return launch1(engine_sweep_kernel<kF32>, tiles, kThreads, stream, args);
-        return launch1(engine_sweep_kernel<kBF16>, tiles, kThreads, stream, args);
+        if (dtype == kF32) return launch1(engine_sweep_kernel<kF32>, tiles, kThreads, stream, args, args.done);
+        return launch1(engine_sweep_kernel<kBF16>, tiles, kThreads, stream, args, args.done);
     }
     if (args.n_rec <= kInlineRecs)
         return portable ? launch_list<true, true>(args, dtype, tiles, stream)

@@ -21,6 +21,7 @@ struct EngineArgs {
     const SeedRec* ext;         // device records when n_rec > kInlineRecs
     uint32_t n_tensors;
     uint32_t n_rec;
+    hipEvent_t done;  // host only: completed by the launch itself, or null
     SeedRec inl[kInlineRecs];
 };
 

@@ -11,6 +11,7 @@
 // quantizer, nf4_ops.hpp).
 #include "engine.hpp"
 #include "engine_launch.hpp"
+#include "launch.hpp"
 #include "nf4_ops.hpp"
 
 namespace mezo {
@@ -269,22 +270,15 @@ __global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_kernel(EngineAr
 }
 
 namespace {
-hipError_t launch1(void (*kernel)(EngineArgs), uint32_t tiles, int lanes, hipStream_t stream, EngineArgs arg)
-{
-    void* params[] = {&arg};
-    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(tiles), dim3(uint32_t(lanes)), params, 0,
-                           stream);
-}
-
 template <bool kPortable, int kDwords>
 hipError_t launch_variant(const EngineArgs& args, uint32_t tiles, hipStream_t stream)
 {
     constexpr int kLanes = kNF4Lanes<kDwords>;
     if (args.n_rec > kInlineRecs)
-        return launch1(engine_nf4_kernel<false, kPortable, kDwords>, tiles, kLanes, stream, args);
-    if (args.n_rec == 1) return launch1(engine_nf4_sweep_kernel<kPortable, kDwords>, tiles, kLanes, stream, args);
-    if (args.n_rec <= 2) return launch1(engine_nf4_short_kernel<kPortable, kDwords>, tiles, kLanes, stream, args);
-    return launch1(engine_nf4_kernel<true, kPortable, kDwords>, tiles, kLanes, stream, args);
+        return launch1(engine_nf4_kernel<false, kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
+    if (args.n_rec == 1) return launch1(engine_nf4_sweep_kernel<kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
+    if (args.n_rec <= 2) return launch1(engine_nf4_short_kernel<kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
+    return launch1(engine_nf4_kernel<true, kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
 }
 
 // Two code dwords per lane from kTilesNF4For2 tiles on, as on dense storage

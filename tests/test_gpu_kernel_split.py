@@ -182,3 +182,32 @@ def test_checksum_runs_across_tensor_ends(mz, orc, dtype, spread):
     assert (a.checksum() + b.checksum()) & 0xFFFFFFFFFFFFFFFF == want
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("types", [[synth.F32], [synth.F32, synth.BF16], [synth.BF16, synth.NF4]])
+@pytest.mark.parametrize("n_rec", [1, 2, 30])
+def test_destroy_waits_for_the_last_launch(mz, types, n_rec):
+    """A call's last launch completes its stream's event: destroying the sets,
+    destination and source, waits for a queue of short calls on two streams."""
+    import torch
+    n = 1 << 22
+
+    def fresh():
+        return mz.ParamSet([mz.NF4Tensor.empty(n) if d == synth.NF4 else
+                            torch.zeros(n, device="cuda", dtype=torch.float32 if d == synth.F32 else torch.bfloat16)
+                            for d in types])
+
+    a, b = fresh(), fresh()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    seeds, scales = records(n_rec, 31)
+    out = torch.zeros(1, dtype=torch.int64, device="cuda")
+    a.checksum(), b.checksum()
+    torch.cuda.synchronize()
+    for _ in range(300):
+        for s in streams:
+            a.perturb_multi(seeds, scales, stream=s)
+    b.perturb_from(a, (1, 2, 3), 1e-3, stream=streams[0])
+    a.checksum_into(out, stream=streams[1])
+    a.close()
+    assert streams[0].query() and streams[1].query()
+    b.close()
