@@ -47,8 +47,10 @@ sys.path.insert(0, ROOT)
 #: lane-instructions per second; transcendentals (log, sqrt, sin, cos) issue
 #: on a unit of their own beside them (their 2 per param-seed take 2 x 8
 #: cycles per wave on it, less than the 13.5 x 4 of the rest), so they add no
-#: time at the ceiling. The counters agree: the dual-issue share of the
-#: engine's VALU cycles (14-15%) is its transcendental share (8 of 62).
+#: time at the ceiling. The chip's own rules differ in both directions
+#: (csrc/engine.hpp): xors, shifts, adds and fmas of two waves can share an
+#: issue slot, transcendentals share none; for this mix they give 226 cycles
+#: per block and wave where this figure gives 216.
 CLOCK_GHZ = 2.4
 VALU_LANE_INSTR_PER_S = 256 * 4 * 16 * CLOCK_GHZ * 1e9
 HBM_PEAK_GBS = 8000.0
