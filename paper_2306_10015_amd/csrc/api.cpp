@@ -209,8 +209,8 @@ struct mezo_paramset {
     std::atomic<uint32_t> gaussian{MEZO_GAUSS_FAST};
     mezo::TensorDesc* d_table[kTypes] = {};
     uint32_t* d_tile_tensor[kTypes] = {};  // tensor index of every tile
-    // One event per stream the paramset's kernels ran on, completed by the
-    // latest launch on that stream itself: destroy waits for all of them before it
+    // One event per stream the paramset's kernels ran on, for the latest
+    // launch on that stream: destroy waits for all of them before it
     // frees the tables (work on an earlier stream may still be running). At
     // most kUses streams are tracked; a further stream takes over the entry
     // used longest ago, after waiting on the host for that entry's event. The
@@ -348,18 +348,33 @@ int use_entry(mezo_paramset* ps, hipStream_t stream, mezo_paramset::Use*& out)
     return MEZO_OK;
 }
 
-// That ps's tables are read by the work just enqueued on the entry's stream,
-// whose last launch completes the entry's event.
-void mark_use(mezo_paramset* ps, mezo_paramset::Use* use) { use->seq = ++ps->use_seq; }
+// Sets from here on have a call's last launch complete the entry's event
+// itself; on smaller ones it is recorded behind the launch. On the 125M fp32
+// set the launch's own event takes one sample's sweeps from 455.7 to 447.2 us
+// and the checksum from 84.9 to 82.2. On 1M elements, where the host sets the
+// pace, thousands of such launches leave a new set's first pass at 180 us
+// against 70-110 (the runtime's bookkeeping of events it has yet to retire).
+constexpr uint64_t kOwnEventElements = uint64_t(1) << 24;
+hipEvent_t own_event(const mezo_paramset* ps, const mezo_paramset::Use* use)
+{
+    return use && ps->numel >= kOwnEventElements ? use->done : nullptr;
+}
 
-// The same for a source set, whose event is recorded after the launch (the
-// launch itself completes its destination's).
+// That ps's tables are read by the work just enqueued on the entry's stream.
+int mark_use(mezo_paramset* ps, mezo_paramset::Use* use)
+{
+    use->seq = ++ps->use_seq;
+    if (!own_event(ps, use)) MEZO_HIP(hipEventRecord(use->done, use->stream));
+    return MEZO_OK;
+}
+
+// The same for a source set, whose event is always recorded.
 int record_use(mezo_paramset* ps, hipStream_t stream)
 {
     mezo_paramset::Use* use = nullptr;
     const int rc = use_entry(ps, stream, use);
     if (rc) return rc;
-    mark_use(ps, use);
+    use->seq = ++ps->use_seq;
     MEZO_HIP(hipEventRecord(use->done, stream));
     return MEZO_OK;
 }
@@ -393,7 +408,7 @@ hipError_t launch_tables(const mezo_paramset* ps, mezo::EngineArgs& args, bool p
         args.src_tensors = src ? src->d_table[dt] : nullptr;
         args.n_tensors = static_cast<uint32_t>(ps->table[dt].size());
         args.total_tiles = ps->total_tiles[dt];
-        args.done = use && dt == last ? use->done : nullptr;
+        args.done = dt == last ? own_event(ps, use) : nullptr;
         e = dt == mezo::kNF4 ? mezo::launch_engine_nf4(args, portable, stream)
                              : mezo::launch_engine_dense(args, dt, portable, stream);
     }
@@ -474,8 +489,8 @@ int launch_records(mezo_paramset* ps, RecSpan recs, bool portable, hipStream_t s
     }
     if (e != hipSuccess) return hip_fail(e, "engine launch");
     if (capture) return MEZO_OK;
-    mark_use(ps, use);
-    return src && src != ps ? record_use(src, stream) : MEZO_OK;
+    rc = mark_use(ps, use);
+    return rc == MEZO_OK && src && src != ps ? record_use(src, stream) : rc;
 }
 
 int launch_records(mezo_paramset* ps, const std::vector<mezo::SeedRec>& recs, bool portable, hipStream_t stream,
@@ -842,8 +857,7 @@ int mezo_replay_noalloc(mezo_paramset_t ps, const mezo_step_t* steps, uint32_t T
         }
         const hipError_t e = launch_tables(ps, args, portable, st, nullptr, use);
         if (e != hipSuccess) return hip_fail(e, "engine launch");
-        if (use) mark_use(ps, use);
-        return MEZO_OK;
+        return use ? mark_use(ps, use) : MEZO_OK;
     });
 }
 
@@ -877,12 +891,11 @@ int mezo_checksum(mezo_paramset_t ps, uint64_t* out_dev, void* stream)
             rc = use_entry(ps, st, use);
             if (rc) return rc;
             pair = static_cast<size_t>(use - ps->uses);
-            for (int i = 0; i < n; ++i) tabs[i].done = use->done;
+            for (int i = 0; i < n; ++i) tabs[i].done = own_event(ps, use);
         }
         MEZO_HIP(mezo::launch_checksum(tabs, dts, n, reinterpret_cast<unsigned long long*>(out_dev),
                                        ps->d_ck + 2 * pair, ps->device, st));
-        if (use) mark_use(ps, use);
-        return MEZO_OK;
+        return use ? mark_use(ps, use) : MEZO_OK;
     });
 }
 
