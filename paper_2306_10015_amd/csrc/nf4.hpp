@@ -21,9 +21,14 @@
 //   and t & kNF4RowMask is 8 b, the byte offset of the row. For |x| <= 1 +
 //   2^-22, b is in [0, 128] with no clamp. A row holds what the code takes in
 //   float arithmetic, whose instructions issue in pairs where compares and
-//   integer packing issue alone: code = lo + clamp(2^40 x + thr, 0, 1) with
-//   thr = -2^40 midpoint (-inf for a row without one), exact: the fma's result
-//   has the sign of x - midpoint, and no two floats here are closer than 2^-40.
+//   integer packing issue alone: code = lo + clamp(2^60 x + thr, 0, 1) with
+//   thr = -2^60 midpoint (-inf for a row without one). The clamp must give 0 or
+//   1 and never a fraction, which would carry into the codes gathered beside
+//   it: the fma has the sign of x - midpoint, and where that is not zero it is
+//   at least 2^8. In a row with a midpoint |x| > 2^-5, so a float x and the
+//   midpoint are multiples of 2^-28; fast mode's x, the unrounded product w r
+//   of two floats, has 48 bits and is a multiple of 2^-52. (r <= 2^64, so 2^60 r
+//   is finite.)
 // - kNF4Table, 128 bins: b(x) = floor(fl32(64 x + 64)) clamped to [0, 127]
 //   (fma rounds 64 x + 64 once, exactly as the double expression below
 //   rounded to float does); the rule the row table is checked against below.
@@ -138,10 +143,10 @@ static_assert(nf4_round_bin_of(-1.00000012f) == 0 && nf4_round_bin_of(1.00000012
 constexpr int kNF4Rows = 129;
 constexpr float kNF4RowMagic = 12583428.0f;  // 1.5 * 2^23 + 516
 constexpr uint32_t kNF4RowMask = 0x7F8u;     // byte offset of the row in t's bit pattern
-constexpr float kNF4Steep = 0x1p40f;
+constexpr float kNF4Steep = 0x1p60f;
 
 struct alignas(8) NF4Row {
-    float thr;  // -2^40 midpoint, or -inf
+    float thr;  // -2^60 midpoint, or -inf
     float lo;   // the code below the midpoint
 };
 
@@ -185,6 +190,14 @@ constexpr NF4RowTable make_nf4_rows()
 constexpr NF4RowTable kNF4RowTable = make_nf4_rows();
 static_assert(kNF4RowTable.ok, "two NF4 midpoints share a row");
 static_assert(nf4_row_of(-1.0f) == 0 && nf4_row_of(1.0f) == kNF4Rows - 1, "row range");
+// |x| > 2^-5 in every row with a midpoint (what the slope is chosen for).
+constexpr bool nf4_rows_near_zero_free()
+{
+    for (int b = nf4_row_of(-0x1p-5f); b <= nf4_row_of(0x1p-5f); ++b)
+        if (kNF4RowTable.row[b].thr != -__builtin_huge_valf()) return false;
+    return true;
+}
+static_assert(nf4_rows_near_zero_free(), "a midpoint's row reaches below 2^-5");
 
 // The code of x by either table.
 constexpr int nf4_row_code(float x)

@@ -3,6 +3,10 @@
 // the host over every float x with 2^-10 <= |x| <= 1 + 2^-22, and the general
 // lookup over special values too. Each code is compared with the number of
 // midpoints strictly below x (read from stdin as in nf4_table_check.cpp).
+// Fast mode's form takes x = w r unrounded: replayed over weights next to the
+// midpoints of blocks of many maxima m, with r = 1 / m and both floats beside
+// it, in gathers of four different elements, each of which must come out with
+// its own code (the product has at most 48 bits, so double compares it exactly).
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -51,6 +55,28 @@ static uint32_t code_general(float x)
     return uint32_t(e.lo) + (std::fmaf(x, kNF4Steep, e.thr) > 0.0f ? 1u : 0u);
 }
 
+// Fast mode's gathered codes of w[0 .. 3] in a block of reciprocal r.
+static uint32_t codes_fast(const float (&w)[4], float r)
+{
+    const float r512 = r * 512.0f, rs = r * kNF4Steep;
+    float g = 0.0f;
+    for (int j = 3; j >= 0; --j) {
+        const uint32_t off = bits(std::fmaf(w[j], r512, kNF4RowMagic)) & kNF4RowMask;
+        if (off / 8 >= uint32_t(kNF4Rows)) return 0xFFFFFFFFu;  // past the table
+        const mezo::NF4Row& e = mezo::kNF4RowTable.row[off / 8];
+        const float up = std::fmin(std::fmax(std::fmaf(w[j], rs, e.thr), 0.0f), 1.0f);
+        g = std::fmaf(j == 3 ? 128.0f : g, 16.0f, e.lo) + up;
+    }
+    return bits(g) & 0xFFFFu;
+}
+
+static uint64_t g_state = 1;
+static uint32_t rnd()
+{
+    g_state = g_state * 6364136223846793005ull + 1442695040888963407ull;
+    return uint32_t(g_state >> 32);
+}
+
 int main()
 {
     float mid[15];
@@ -80,6 +106,42 @@ int main()
         if (std::fabs(x) <= 1.0f) bad += code_usual(x) != w;
         ++n;
     }
+    // fast mode: four different elements against their own codes, the one next
+    // to a midpoint in every place of the gather
+    unsigned long long fast = 0, bad_fast = 0;
+    const auto want_product = [&](float w, float r) {
+        uint32_t c = 0;
+        for (int i = 0; i < 15; ++i) c += double(mid[i]) < double(w) * double(r) ? 1u : 0u;
+        return c;
+    };
+    const auto check_fast = [&](float near, float m, float r, int place) {
+        float w[4];
+        for (int j = 0; j < 4; ++j) w[j] = m * (float(int32_t(rnd())) * 0x1p-31f);
+        w[(place + 1) & 3] = 0.0f;
+        w[place] = near;
+        uint32_t c = 0;
+        for (int j = 0; j < 4; ++j) c |= want_product(w[j], r) << (4 * j);
+        ++fast;
+        bad_fast += codes_fast(w, r) != c;
+    };
+    // products a hair above a midpoint
+    const float pairs[][2] = {{0x1.60bc6cp-5f, 0x1.c1222cp-10f}, {0x1.4a47d6p-5f, -0x1.6c657ep-8f}};
+    for (const auto& p : pairs)
+        for (int place = 0; place < 4; ++place) check_fast(p[1], p[0], 1.0f / p[0], place);
+    for (uint32_t k = 0; k < (1u << 21); ++k) {
+        // a maximum in [2^-64, 2^64), one in eight of an ordinary weight's size
+        const int ex = k & 7 ? int(rnd() % 128u) - 64 : -5;
+        const float m = std::ldexp(1.0f + float(rnd() >> 9) * 0x1p-23f, ex);
+        const float inv = 1.0f / m;
+        for (int d = -1; d <= 1; ++d) {
+            const float r = from_bits(bits(inv) + uint32_t(d));
+            const int i = int(rnd() % 15u);
+            const float at = float(double(mid[i]) / double(r));
+            for (int e = -1; e <= 1; ++e) check_fast(from_bits(bits(at) + uint32_t(e)), m, r, int(k & 3u));
+        }
+    }
+    std::printf("fast mode: %llu gathers, %llu wrong\n", fast, bad_fast);
+    bad += bad_fast;
     std::printf("%llu values, %llu mismatches\n", n, bad);
     return bad ? 1 : 0;
 }
