@@ -164,17 +164,23 @@ struct RunCursor {
 };
 
 // fp32/bf16 tensors. Workgroup b takes the run of consecutive tiles
-// [T b / G, T (b + 1) / G) of the table's T tiles (G workgroups, two per CU):
-// the descriptor changes only where the run crosses into the next tensor (no
-// per-tile map lookup). Tiles go in groups of eight: the eight loads are
-// issued before any is mixed, eight 16-byte loads in flight per lane. Groups
-// that cross a tensor's end and the run's last, shorter one go through
-// mix_any_tiles; one tile at a time instead, each waiting for its descriptor
-// and its data, the 125M fp32 call took 87.1 against 84.9 us. Few workgroups with many loads each
-// stream faster than many with few: against eight workgroups per CU with
-// two tiles in flight, the 125M fp32 set took 0.093 -> 0.085 ms and the 6.7B
-// bf16 set 1.96 -> 1.90 ms (paired runs, checksums identical; one workgroup
-// per CU or sixteen tiles in flight were slower).
+// [T b / G, T (b + 1) / G) of the table's T tiles (G workgroups, two per CU).
+// Tiles go in groups of eight: the eight loads are issued before any is mixed,
+// eight 16-byte loads in flight per lane. A group wholly inside a tensor uses
+// the cursor's descriptor, which changes only where the run crosses into
+// another tensor. Groups that cross a tensor's end and the run's last, shorter
+// one read map and descriptors of all their tiles (mix_any_tiles): one tile at
+// a time instead, each waiting for its descriptor and its data, the 125M fp32
+// call took 82.6 against 79.7 us. Up to four last tiles go one at a time
+// all the same: that is all that small sets have, and there the long group's
+// code, run once, costs more than its loads save (calls on 1M elements fp32
+// and bf16 20.2 -> 18.6 and 20.1 -> 18.4 us, 100 thousand fp32 10.0 -> 8.3;
+// three tiles 20.3 -> 18.9, four 20.3 -> 19.1, from five on equal; 125M 79.7).
+// Few workgroups with many loads each stream faster than many with few:
+// against eight workgroups per CU with two tiles in flight, the 125M fp32 set
+// took 0.093 -> 0.085 ms and the 6.7B bf16 set 1.96 -> 1.90 ms (paired runs,
+// checksums identical; one workgroup per CU or sixteen tiles in flight were
+// slower).
 template <uint32_t kDtype>
 __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
 {
@@ -183,6 +189,7 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
     constexpr uint64_t kEsz = 16 / kPer;
     constexpr uint64_t kTileElems = uint64_t(kThreads) * kPer;
     constexpr uint64_t kInFlight = 8;  // tiles whose loads a lane issues before mixing any
+    constexpr uint64_t kShortRun = 4;  // last tiles taken one at a time
     // chunk number of the lane's first chunk within its tile, times kChunkPos;
     // opaque from here on: otherwise the compiler folds uniform + lane
     // constant back into one per-lane 64-bit multiply in every tile
@@ -208,6 +215,17 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
 #pragma unroll
                 for (uint64_t j = 0; j < kInFlight; ++j)
                     sum += mix_whole_tile(v[j], cpos + j * (2 * kThreads * kChunkPos), tmix, cpos_lane);
+            } else if (t + kShortRun >= t_end) {
+                for (uint64_t k = t; k < t_end; ++k) {
+                    c.seek(k);
+                    const uint64_t at = k - c.begin;
+                    if ((at + 1) * kTileElems <= c.numel)
+                        sum += mix_whole_tile(load_whole_tile(c.data, at),
+                                              (c.first * kEsz / 8 + 2 * at * kThreads) * kChunkPos,
+                                              uint64_t(c.id) * kChunkTensor, cpos_lane);
+                    else
+                        sum += mix_any_tiles<kDtype, 1u>(a, k, 1u, cpos_lane);
+                }
             } else {
                 const uint64_t n = t_end - t < kInFlight ? t_end - t : kInFlight;
                 sum += mix_any_tiles<kDtype, uint32_t(kInFlight)>(a, t, uint32_t(n), cpos_lane);
