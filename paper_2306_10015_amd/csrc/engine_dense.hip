@@ -272,7 +272,10 @@ hipError_t launch_blocks(const EngineArgs& args, uint32_t tiles, hipStream_t str
 // on 16M: 452 -> 426, 432, 453). bf16 with 2, 4: 8M 35.1 -> 33.0, 34.1; 16M
 // 62.1 -> 58.4, 58.5; 32M 116.1 -> 109.1, 107.6; 64M 224.1 -> 210.8, 205.3.
 // Portable, fp32 with 1, 2: 16M 113.2 -> 89.2, 96.7; 128M 864 -> 680, 670;
-// bf16 gains from 2 at every size (4: 4-7% slower).
+// bf16 gains from 2 at every size (4: 4-7% slower). One portable record on fp32
+// is bound by memory too and keeps 1 at every size: one group per lane without
+// phases, 1, 2: 130M 169.9, 165.9, 169.4 us; 300M 383.5, 378.3, 390.0; 520M
+// 662, 654, 683 (two records: 520M 1039, 878, 839).
 constexpr uint32_t kTilesF32For2 = 24u << 10, kTilesF32For4 = 96u << 10, kTilesBF16For4 = 8u << 10;
 constexpr uint32_t kTilesF32PortableFor2 = 64u << 10;
 
@@ -281,7 +284,8 @@ hipError_t launch_list(const EngineArgs& args, uint32_t dtype, uint32_t tiles, h
 {
     if (dtype == kF32) {
         if constexpr (kPortable) {
-            if (tiles < kTilesF32PortableFor2) return launch_blocks<kInline, kF32, true, 1>(args, tiles, stream);
+            if (tiles < kTilesF32PortableFor2 || args.n_rec == 1)
+                return launch_blocks<kInline, kF32, true, 1>(args, tiles, stream);
             return launch_blocks<kInline, kF32, true, 2>(args, tiles, stream);
         } else {
             if (tiles < kTilesF32For2) return launch_blocks<kInline, kF32, false, 1>(args, tiles, stream);
