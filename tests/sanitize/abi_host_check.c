@@ -7,7 +7,9 @@
  * (Section 3) over every code, the records a call hands to the engine
  * (coefficients, zero terms dropped, step ends flagged), staging of long
  * record lists through the slot ring and its growth, replay split at step
- * ends, per-stream event bookkeeping, device and graph-capture refusals, a
+ * ends, per-stream event bookkeeping, what destroy and a taken-over entry wait
+ * for (the stand-in ends the program where memory is freed or shared under
+ * unfinished work), device and graph-capture refusals, a
  * failed device allocation, and concurrent callers. Every paramset is
  * destroyed at the end, and every "device" allocation and event must be gone.
  * Exit status 0 when every check passed. */
@@ -29,6 +31,7 @@ unsigned long double_checksum_launches(void);
 unsigned long double_nf4_launches(void);
 unsigned long double_generate_launches(void);
 unsigned long double_event_syncs(void);
+unsigned long double_unfinished_uses(void);
 unsigned long double_events_live(void);
 size_t double_device_allocations(void);
 unsigned long double_allocation_calls(void);
@@ -453,6 +456,73 @@ static void check_streams_devices_capture(void)
     free(q);
 }
 
+/* what is waited for: sets whose event is recorded behind a call and sets whose
+ * event the call's last launch completes itself (2^24 elements on), of one and
+ * of three storage types */
+static void check_waits(void)
+{
+    const uint64_t sizes[4] = {3000, ((uint64_t)1 << 24) - 1, (uint64_t)1 << 24, ((uint64_t)1 << 24) + 70001};
+    mezo_codec_t c = {MEZO_CODEC_LINEAR, 1.0f / 127.0f, 0.0f};
+    mezo_seed_t* s = seeds_n(64, 0);
+    int8_t* q = codes_n(64, 0);
+    uint64_t out;
+    int i, three, last;
+    for (i = 0; i < 4; ++i)
+        for (three = 0; three < 2; ++three)
+            for (last = 0; last < 5; ++last) {
+                void *const a = (void*)0x100, *const b = (void*)0x200;
+                mezo_paramset_t ps, src, one[2];
+                mezo_tensor_t t[3];
+                unsigned long syncs;
+                uintptr_t k;
+                int j;
+                for (j = 0; j < 2; ++j) {
+                    const uintptr_t at = (uintptr_t)(j + 1) << 40;
+                    t[0] = T(at, sizes[i] - (three ? 2000 : 0), 0, MEZO_F32, 0, 0);
+                    t[1] = T(at + ((uintptr_t)1 << 36), 1000, 1, MEZO_BF16, 0, 0);
+                    t[2] = T(at + ((uintptr_t)2 << 36), 1000, 2, MEZO_NF4, at + ((uintptr_t)3 << 36), 0);
+                    CHECK(mezo_paramset_create(t, three ? 3 : 1, &one[j]) == MEZO_OK);
+                }
+                ps = one[0];
+                src = one[1];
+                CHECK(mezo_paramset_numel(ps) == sizes[i]);
+                /* two streams, each kind of call in turn the last of them */
+                CHECK(mezo_perturb(src, S(9, 0, 0), 1e-3f, b) == MEZO_OK);
+                CHECK(mezo_perturb(ps, S(9, 0, 0), 1e-3f, a) == MEZO_OK);
+                for (j = 0; j < 5; ++j) {
+                    const int op = (last + 1 + j) % 5;
+                    void* st = j % 2 ? a : b;
+                    if (op == 0) CHECK(mezo_perturb(ps, S(1, 0, 0), 1e-3f, st) == MEZO_OK);
+                    if (op == 1) CHECK(mezo_update_multi(ps, s, q, 40, &c, 1e-4f, st) == MEZO_OK);
+                    if (op == 2) CHECK(mezo_checksum(ps, &out, st) == MEZO_OK);
+                    if (op == 3) CHECK(mezo_perturb_from(ps, src, S(2, 0, 0), 1e-3f, st) == MEZO_OK);
+                    if (op == 4) {
+                        mezo_step_t step;
+                        memset(&step, 0, sizeof(step));
+                        step.seeds = s;
+                        step.q = q;
+                        step.K = 64;
+                        step.lr = 1e-4f;
+                        CHECK(mezo_replay_noalloc(ps, &step, 1, &c, st) == MEZO_OK);
+                    }
+                }
+                CHECK(double_unfinished_uses() > 0);
+                /* more streams than entries: each takeover waits for the one
+                 * entry's work, and no running sum is shared */
+                if (last == 2) {
+                    for (k = 3; k <= 16; ++k) CHECK(mezo_checksum(ps, &out, (void*)(k * 0x100)) == MEZO_OK);
+                    syncs = double_event_syncs();
+                    for (k = 17; k <= 36; ++k) CHECK(mezo_checksum(ps, &out, (void*)(k * 0x100)) == MEZO_OK);
+                    CHECK(double_event_syncs() == syncs + 20);
+                }
+                mezo_paramset_destroy(last % 2 ? ps : src);
+                mezo_paramset_destroy(last % 2 ? src : ps);
+                CHECK(double_unfinished_uses() == 0);
+            }
+    free(s);
+    free(q);
+}
+
 static void check_from_mixed_checksum_nf4(void)
 {
     mezo_paramset_t dst, src, bad, overlap, mixed;
@@ -571,6 +641,7 @@ int main(void)
     check_perturb_calls();
     check_staging_and_replay();
     check_streams_devices_capture();
+    check_waits();
     check_replay_noalloc();
     check_from_mixed_checksum_nf4();
     check_inspection_and_messages();

@@ -4,7 +4,11 @@
 // UndefinedBehaviorSanitizer and driven on a machine without a GPU.
 //
 // "Device" memory is host memory from malloc, tracked by address and size;
-// events are heap objects; streams are opaque tokens. A "launch" runs no
+// events are heap objects; streams are opaque tokens. Work enqueued on a stream
+// stays unfinished until the host waits for an event behind it: freeing memory
+// that unfinished work uses, refilling a staging slot under it, or handing a
+// running sum to a second stream ends the program (hipFree here waits for
+// nothing, where the runtime's may). A "launch" runs no
 // kernel: it reads every byte the real kernel would read from the library's
 // own device tables and staged record lists (so a bookkeeping mistake there is
 // an out-of-bounds or use-after-free read the sanitizer reports), checks that
@@ -12,10 +16,12 @@
 // driver (abi_host_check.c) to inspect through the double_* functions.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <vector>
@@ -57,7 +63,8 @@ int g_last_out_of_place = 0;
 
 struct Event {
     uint32_t magic;
-    int recorded;
+    hipStream_t stream;  // what it stands behind: the first `upto` pieces of
+    uint64_t upto;       // work of this stream
 };
 constexpr uint32_t kEventMagic = 0x45564E54u;
 
@@ -75,6 +82,51 @@ bool inside(const std::map<uintptr_t, size_t>& m, const void* p, size_t bytes)
     if (it == m.begin()) return false;
     --it;
     return a >= it->first && a + bytes <= it->first + it->second;
+}
+
+// Work enqueued on each stream and how much of it is known to be finished, and
+// the memory that enqueued work uses.
+struct Queue {
+    uint64_t enqueued = 0, finished = 0;
+};
+std::map<hipStream_t, Queue> g_queues;
+struct MemoryUse {
+    uintptr_t at;
+    hipStream_t stream;
+    uint64_t number;  // the stream's piece of work
+};
+std::vector<MemoryUse> g_uses;
+
+bool unfinished(const MemoryUse& u) { return u.number > g_queues[u.stream].finished; }
+
+// One more piece of work on stream using the given addresses (g_mu held). A
+// captured one runs with its graph, which the caller waits for. done: an event
+// the work completes itself, or null.
+void enqueue(hipStream_t stream, std::initializer_list<const void*> uses, hipEvent_t done)
+{
+    if (g_capturing) {
+        if (done) fail("a captured launch completes an event");
+        return;
+    }
+    const uint64_t number = ++g_queues[stream].enqueued;
+    for (const void* p : uses)
+        if (p) g_uses.push_back({reinterpret_cast<uintptr_t>(p), stream, number});
+    if (done) {
+        Event* ev = reinterpret_cast<Event*>(done);
+        if (ev->magic != kEventMagic) fail("a launch completes a destroyed or foreign event");
+        ev->stream = stream;
+        ev->upto = number;
+    }
+}
+
+// Whether unfinished work uses an address in [p, p + bytes) (g_mu held); other:
+// work of streams other than this one only.
+bool busy(const void* p, size_t bytes, const hipStream_t* other = nullptr)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+    for (const auto& u : g_uses)
+        if (u.at >= a && u.at < a + bytes && unfinished(u) && !(other && u.stream == *other)) return true;
+    return false;
 }
 
 // Read every byte of [p, p + bytes) (the sanitizer checks each access).
@@ -133,7 +185,10 @@ hipError_t hipFree(void* p)
 {
     std::lock_guard<std::mutex> lock(g_mu);
     if (!p) return hipSuccess;
-    if (!g_dev.erase(reinterpret_cast<uintptr_t>(p))) fail("hipFree of an address hipMalloc did not return");
+    const auto it = g_dev.find(reinterpret_cast<uintptr_t>(p));
+    if (it == g_dev.end()) fail("hipFree of an address hipMalloc did not return");
+    if (busy(p, it->second)) fail("hipFree of memory that unfinished work uses");
+    g_dev.erase(it);
     std::free(p);
     return hipSuccess;
 }
@@ -152,7 +207,10 @@ hipError_t hipHostFree(void* p)
 {
     std::lock_guard<std::mutex> lock(g_mu);
     if (!p) return hipSuccess;
-    if (!g_host.erase(reinterpret_cast<uintptr_t>(p))) fail("hipHostFree of an address hipHostMalloc did not return");
+    const auto it = g_host.find(reinterpret_cast<uintptr_t>(p));
+    if (it == g_host.end()) fail("hipHostFree of an address hipHostMalloc did not return");
+    if (busy(p, it->second)) fail("hipHostFree of memory that an unfinished copy reads");
+    g_host.erase(it);
     std::free(p);
     return hipSuccess;
 }
@@ -167,13 +225,15 @@ hipError_t hipMemcpy(void* dst, const void* src, size_t bytes, hipMemcpyKind kin
     return hipSuccess;
 }
 
-hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind kind, hipStream_t)
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind kind, hipStream_t stream)
 {
     std::lock_guard<std::mutex> lock(g_mu);
     if (kind != hipMemcpyHostToDevice) fail("unexpected copy direction");
     if (!inside(g_dev, dst, bytes)) fail("hipMemcpyAsync past a device allocation");
     if (!inside(g_host, src, bytes)) fail("hipMemcpyAsync from outside a pinned host allocation");
+    if (busy(src, bytes) || busy(dst, bytes)) fail("a staging slot is refilled under unfinished work");
     std::memcpy(dst, src, bytes);
+    enqueue(stream, {dst, src}, nullptr);
     g_stats.h2d_bytes += bytes;
     return hipSuccess;
 }
@@ -186,7 +246,7 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st)
 
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned)
 {
-    Event* ev = new Event{kEventMagic, 0};
+    Event* ev = new Event{kEventMagic, nullptr, 0};
     *e = reinterpret_cast<hipEvent_t>(ev);
     std::lock_guard<std::mutex> lock(g_mu);
     ++g_stats.events_live;
@@ -194,11 +254,13 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned)
     return hipSuccess;
 }
 
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t)
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t stream)
 {
     Event* ev = reinterpret_cast<Event*>(e);
     if (!ev || ev->magic != kEventMagic) fail("hipEventRecord on a destroyed or foreign event");
-    ev->recorded = 1;
+    std::lock_guard<std::mutex> lock(g_mu);
+    ev->stream = stream;
+    ev->upto = g_queues[stream].enqueued;
     return hipSuccess;
 }
 
@@ -208,6 +270,12 @@ hipError_t hipEventSynchronize(hipEvent_t e)
     if (!ev || ev->magic != kEventMagic) fail("hipEventSynchronize on a destroyed or foreign event");
     std::lock_guard<std::mutex> lock(g_mu);
     ++g_stats.event_syncs;
+    if (ev->upto) {
+        Queue& q = g_queues[ev->stream];
+        if (ev->upto > q.finished) q.finished = ev->upto;
+    }
+    g_uses.erase(std::remove_if(g_uses.begin(), g_uses.end(), [](const MemoryUse& u) { return !unfinished(u); }),
+                 g_uses.end());
     return hipSuccess;
 }
 
@@ -229,7 +297,7 @@ hipError_t hipEventDestroy(hipEvent_t e)
 namespace mezo {
 
 namespace {
-hipError_t engine(const EngineArgs& a, uint32_t dtype)
+hipError_t engine(const EngineArgs& a, uint32_t dtype, hipStream_t stream)
 {
     std::lock_guard<std::mutex> lock(g_mu);
     check_table(a.tensors, a.n_tensors, a.tile_tensor, a.total_tiles);
@@ -250,26 +318,28 @@ hipError_t engine(const EngineArgs& a, uint32_t dtype)
     g_last_recs.assign(recs, recs + a.n_rec);
     g_last_dtype = dtype;
     g_last_out_of_place = a.src_tensors != nullptr;
+    enqueue(stream, {a.tensors, a.tile_tensor, a.src_tensors, a.n_rec > kInlineRecs ? a.ext : nullptr}, a.done);
     ++g_stats.launches[dtype];
     return hipSuccess;
 }
 }  // namespace
 
-hipError_t launch_engine_dense(const EngineArgs& a, uint32_t dtype, bool, hipStream_t)
+hipError_t launch_engine_dense(const EngineArgs& a, uint32_t dtype, bool, hipStream_t stream)
 {
     if (dtype != kF32 && dtype != kBF16) fail("dense launch of another storage type");
-    return engine(a, dtype);
+    return engine(a, dtype, stream);
 }
 
-hipError_t launch_engine_nf4(const EngineArgs& a, bool, hipStream_t) { return engine(a, kNF4); }
+hipError_t launch_engine_nf4(const EngineArgs& a, bool, hipStream_t stream) { return engine(a, kNF4, stream); }
 
 hipError_t launch_checksum(const ChecksumArgs* tables, const uint32_t* dtypes, int n, unsigned long long* out,
-                           unsigned long long* acc, int, hipStream_t)
+                           unsigned long long* acc, int, hipStream_t stream)
 {
     std::lock_guard<std::mutex> lock(g_mu);
     // the running sum: two words of a device allocation, zero between calls
     if (!inside(g_dev, acc, 2 * sizeof(*acc))) fail("checksum running sum outside a device allocation");
     if (acc[0] != 0 || acc[1] != 0) fail("checksum running sum not zero at a call");
+    if (!g_capturing && busy(acc, 2 * sizeof(*acc), &stream)) fail("checksums of two streams share a running sum");
     (void)out;
     for (int i = 0; i < n; ++i) {
         const TensorDesc* t = tables[i].tensors;
@@ -283,6 +353,8 @@ hipError_t launch_checksum(const ChecksumArgs* tables, const uint32_t* dtypes, i
         check_table(t, cnt, tables[i].tile_tensor, tables[i].total_tiles);
         for (uint32_t k = 0; k < cnt; ++k)
             if (t[k].dtype != dtypes[i]) fail("checksum table of mixed storage types");
+        // (only the call's last launch completes an event)
+        enqueue(stream, {tables[i].tensors, tables[i].tile_tensor, acc}, i == n - 1 ? tables[i].done : nullptr);
     }
     ++g_stats.checksum_launches;
     return hipSuccess;
@@ -346,6 +418,14 @@ unsigned long double_checksum_launches(void) { return g_stats.checksum_launches;
 unsigned long double_nf4_launches(void) { return g_stats.nf4_launches; }
 unsigned long double_generate_launches(void) { return g_stats.generate_launches; }
 unsigned long double_event_syncs(void) { return g_stats.event_syncs; }
+// Memory uses of work that no wait has covered yet.
+unsigned long double_unfinished_uses(void)
+{
+    std::lock_guard<std::mutex> lock(g_mu);
+    unsigned long n = 0;
+    for (const auto& u : g_uses) n += unfinished(u) ? 1 : 0;
+    return n;
+}
 unsigned long double_events_live(void) { return g_stats.events_live; }
 size_t double_device_allocations(void)
 {
