@@ -38,6 +38,28 @@ def hosts(dtype, seed=3):
     return [synth.theta0_tensor((n,), dtype, 7 + i, seed) for i, n in enumerate(SIZES)]
 
 
+def assert_few_codes_differ(a, b, sizes, n_rec):
+    """4-bit storage in fast mode: calls of one record round the quantizer
+    differently from lists, so a code may differ where x lies within about 2^-22
+    of a midpoint. At 15 midpoints and a density of x below 0.8 that is at most
+    5.7e-6 of the elements in each of the n_rec steps (twice that and 4 blocks
+    are allowed; an element that becomes its block's largest takes the block
+    along). All other blocks: every code equal, the absmax within 2^-22 a
+    step."""
+    import torch
+
+    def blocks_of(t, n):
+        c = torch.stack([t.codes & 15, t.codes >> 4], dim=1).reshape(-1)
+        return torch.nn.functional.pad(c[:n], (0, -n % 64)).reshape(-1, 64)
+
+    differing = 0
+    for x, y, n in zip(a, b, sizes):
+        same = (blocks_of(x, n) == blocks_of(y, n)).all(dim=1)
+        differing += int((~same).sum())
+        assert bool((((x.absmax - y.absmax).abs() <= n_rec * 2.0**-22 * y.absmax) | ~same).all()), n
+    assert differing <= 4 + 2 * 5.7e-6 * n_rec * sum(sizes)
+
+
 @pytest.mark.parametrize("gaussian", ["fast", "portable"])
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16, synth.NF4])
 @pytest.mark.parametrize("n_rec", [3, 40])
@@ -62,13 +84,13 @@ def test_list_kernel_matches_single_record_calls(mz, dtype, n_rec, gaussian):
     for s, c in zip(seeds, scales):
         pb.perturb(s, c)
     torch.cuda.synchronize()
+    if dtype == synth.NF4 and gaussian == "fast":
+        assert_few_codes_differ(a, b, SIZES, n_rec)
+        pa.close()
+        pb.close()
+        return
     for n, x, y in zip(SIZES, a, b):
-        if dtype == synth.NF4 and gaussian == "fast":
-            # 4-bit storage in fast mode: one-record calls may round the
-            # quantizer differently; the values stay close
-            u, v = mz.nf4_dequantize(x).cpu().numpy(), mz.nf4_dequantize(y).cpu().numpy()
-            assert np.mean(np.abs(u - v) > 1e-4) <= 2.0 / min(len(u), 64), n
-        elif dtype == synth.NF4:
+        if dtype == synth.NF4:
             assert torch.equal(x.codes, y.codes) and torch.equal(x.absmax, y.absmax), n
         else:
             assert np.array_equal(to_host(x).view(np.uint8), to_host(y).view(np.uint8)), n
@@ -147,12 +169,8 @@ def test_list_kernels_of_large_sets(mz, dtype, tiles, gaussian):
                 assert torch.equal(x.view(same), y.view(same)), (big_tiles, n)
             elif gaussian == "portable":
                 assert torch.equal(x.codes, y.codes) and torch.equal(x.absmax, y.absmax), (big_tiles, n)
-            else:
-                # one-record calls may round the quantizer differently: a code
-                # here and there, never more
-                d = (mz.nf4_dequantize(x) - mz.nf4_dequantize(y)).abs() > 1e-4
-                assert float(d.float().mean()) <= max(2.0 / min(n, 64), 0.0) if n < 4096 else float(
-                    d.float().mean()) <= 1e-4, (big_tiles, n)
+        if dtype == synth.NF4 and gaussian == "fast":
+            assert_few_codes_differ(a, b, sizes, 3)
         pa.close()
         pb.close()
 
