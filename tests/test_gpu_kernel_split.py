@@ -204,10 +204,12 @@ def test_checksum_runs_across_tensor_ends(mz, orc, dtype, spread):
 
 @pytest.mark.parametrize("types", [[synth.F32], [synth.F32, synth.BF16], [synth.BF16, synth.NF4]])
 @pytest.mark.parametrize("n_rec,n", [(1, 1 << 22), (2, 1 << 24), (30, 1 << 22), (30, 1 << 24)])
-def test_destroy_waits_for_the_last_launch(mz, types, n_rec, n):
-    """A call's last launch completes its stream's event, or on small sets it is
-    recorded behind the launch: destroying the sets, destination and source,
-    waits for a queue of short calls on two streams."""
+def test_destroy_with_queued_calls(mz, types, n_rec, n):
+    """Sets, destination and source, destroyed with a queue of short calls on two
+    streams still running: nothing they use goes first, and the streams are
+    drained. (Freeing device memory waits for the device by itself, so this
+    cannot tell whether destroy's own waits are right: the host check on the
+    CPU does, tests/sanitize/abi_host_check.c, check_waits.)"""
     import torch
 
     def fresh():
@@ -229,3 +231,52 @@ def test_destroy_waits_for_the_last_launch(mz, types, n_rec, n):
     a.close()
     assert streams[0].query() and streams[1].query()
     b.close()
+
+
+@pytest.mark.parametrize("n", [1 << 20, (1 << 24) + 1029])
+@pytest.mark.parametrize("last", ["checksum", "perturb"])
+@pytest.mark.parametrize("dtypes", [[synth.F32], [synth.BF16, synth.F32]])
+def test_a_taken_over_entry_waits_for_its_work(mz, orc, dtypes, last, n):
+    """The first stream's last call on a set, a checksum or a perturbation, waits
+    behind a long queue of another set's work; fifteen more streams use the set;
+    the seventeenth takes the first one's entry and its running sum, and must
+    wait on the host for that call: its own checksum then sees the perturbed
+    weights, and what it leaves on its stream the first stream's result. On both
+    routes of the entry's event: recorded behind the call, or completed by the
+    call's last launch (2^24 elements on)."""
+    import torch
+    src_h = [synth.theta0_tensor((n if i == 0 else 5001,), d, i, 4) for i, d in enumerate(dtypes)]
+    devs = [to_device(h) for h in src_h]
+    ps = mz.ParamSet(devs)
+    seed, scale = (3, 1, 4), 1e-3
+    other = mz.ParamSet([torch.zeros(1 << 26, device="cuda")])
+    seeds, _ = records(30, 5)
+    q = synth.grads_int8(30, seed=5)
+    streams = [torch.cuda.Stream() for _ in range(17)]
+    outs = torch.zeros(17, dtype=torch.int64, device="cuda")
+    # the tables and every stream's queue are made before the clock runs
+    other.update_multi(seeds, q, 1e-3)
+    ps.checksum_into(outs[:1], stream=streams[0])
+    for s in streams:
+        s.wait_stream(streams[0])
+        with torch.cuda.stream(s):
+            outs.zero_()
+    torch.cuda.synchronize()
+    for _ in range(60):  # tens of milliseconds
+        other.update_multi(seeds, q, 1e-3, stream=streams[0])
+    if last == "checksum":
+        ps.checksum_into(outs[:1], stream=streams[0])
+    else:
+        ps.perturb(seed, scale, stream=streams[0])
+    for i in range(1, 16):
+        ps.checksum_into(outs[i:i + 1], stream=streams[i])
+    assert not streams[0].query()
+    ps.checksum_into(outs[16:], stream=streams[16])
+    with torch.cuda.stream(streams[16]):
+        got = [int(v) & 0xFFFFFFFFFFFFFFFF for v in outs[::16].tolist()]
+    torch.cuda.synchronize()
+    want = orc.checksum([to_host(t) for t in devs])
+    assert got == [want if last == "checksum" else 0, want]
+    assert ps.checksum() == want
+    ps.close()
+    other.close()
