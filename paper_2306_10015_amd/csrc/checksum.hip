@@ -184,7 +184,6 @@ struct RunCursor {
 template <uint32_t kDtype>
 __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
 {
-    static_assert(Layout<kDtype>::kGroups == 1, "one 16-byte group per lane");
     constexpr uint64_t kPer = Layout<kDtype>::kPerGroup;
     constexpr uint64_t kEsz = 16 / kPer;
     constexpr uint64_t kTileElems = uint64_t(kThreads) * kPer;

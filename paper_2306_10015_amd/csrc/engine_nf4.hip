@@ -274,8 +274,10 @@ template <bool kPortable, int kDwords>
 hipError_t launch_variant(const EngineArgs& args, uint32_t tiles, hipStream_t stream)
 {
     constexpr int kLanes = kNF4Lanes<kDwords>;
-    if (args.n_rec > kInlineRecs)
-        return launch1(engine_nf4_kernel<false, kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
+    // (two dwords in portable mode are for short lists: launch_dwords)
+    if constexpr (!(kPortable && kDwords == 2))
+        if (args.n_rec > kInlineRecs)
+            return launch1(engine_nf4_kernel<false, kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
     if (args.n_rec == 1) return launch1(engine_nf4_sweep_kernel<kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
     if (args.n_rec <= 2) return launch1(engine_nf4_short_kernel<kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
     return launch1(engine_nf4_kernel<true, kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
@@ -291,6 +293,7 @@ hipError_t launch_variant(const EngineArgs& args, uint32_t tiles, hipStream_t st
 // 4744, 4867), but for short lists on large sets (one record on 1.3B: 1440 ->
 // 1097, 1047; three on 128M 363.5 -> 266.1, 262.9).
 constexpr uint32_t kTilesNF4For2 = 12u << 10, kTilesNF4PortableFor2 = 48u << 10, kRecsNF4PortableFor2 = 4;
+static_assert(kRecsNF4PortableFor2 <= kInlineRecs, "launch_variant has no staged kernel for these");
 
 hipError_t launch_dwords(const EngineArgs& args, bool portable, uint32_t tiles, hipStream_t stream)
 {

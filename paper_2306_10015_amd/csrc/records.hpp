@@ -37,19 +37,18 @@ constexpr uint32_t kBF16 = 1u;
 constexpr uint32_t kNF4 = 2u;
 constexpr uint32_t kStorageTypes = 3u;
 
-// Work decomposition: a workgroup of kThreads lanes handles one tile; each
-// lane owns kGroups 16-byte groups of the tile, strided by kThreads groups so
-// that every wave touches one contiguous 1 KiB run per group. A 16-byte group
-// is 4 fp32 elements (one Philox block) or 8 bf16 elements (two blocks). One
-// group per lane (4 KiB tiles: 1024 fp32 or 2048 bf16 elements) streams
-// faster than two: more workgroups in flight per byte.
+// Work decomposition: one workgroup handles one tile of kThreads 16-byte
+// groups (4 KiB). A 16-byte group is 4 fp32 elements (one Philox block) or 8
+// bf16 elements (two blocks). Sweeps of one or two records and the checksum
+// take kThreads lanes with one group each; record lists fewer lanes with up to
+// four groups each, strided by the lanes so that every access of a wave is one
+// contiguous run (engine_dense.hip).
 constexpr int kThreads = 256;
-constexpr int kGroupsF32 = 1;
-constexpr int kGroupsBF16 = 1;
-constexpr uint64_t kTileF32 = uint64_t(kThreads) * kGroupsF32 * 4;
-constexpr uint64_t kTileBF16 = uint64_t(kThreads) * kGroupsBF16 * 8;
-// NF4: each lane owns 8 consecutive elements (4 code bytes, two Philox
-// blocks); 8 lanes make one block of kNF4Block elements sharing one absmax.
+constexpr uint64_t kTileF32 = uint64_t(kThreads) * 4;
+constexpr uint64_t kTileBF16 = uint64_t(kThreads) * 8;
+// NF4: a tile is 2048 elements, 32 blocks of kNF4Block elements that share one
+// absmax each. A lane owns 8 or 16 consecutive elements (one or two code
+// dwords) in the engine, 8 in the conversions (nf4_ops.hpp).
 constexpr uint64_t kTileNF4 = uint64_t(kThreads) * 8;
 constexpr int kNF4Block = 64;
 
