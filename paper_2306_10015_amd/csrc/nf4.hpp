@@ -87,13 +87,10 @@ constexpr int nf4_round_bin_of(float x)
     return d > 0.5 ? f + 1 : (d < 0.5 ? f : (f % 2 == 0 ? f : f + 1));
 }
 
-// One bin: its midpoint (+inf if none), the code below it and the values of
-// that code and the next.
-struct alignas(16) NF4Bin {
+// One bin: its midpoint (+inf if none) and the code below it.
+struct alignas(8) NF4Bin {
     float mid;
     uint32_t lo;
-    float v_lo;
-    float v_hi;
 };
 
 template <int kBins>
@@ -122,8 +119,6 @@ constexpr NF4Table<kBins> make_nf4_table()
         if (in_bin > 1) t.ok = false;
         t.bin[b].mid = mid;
         t.bin[b].lo = lo;
-        t.bin[b].v_lo = kNF4Values[lo];
-        t.bin[b].v_hi = kNF4Values[lo + 1 < kNF4Codes ? lo + 1 : lo];
     }
     return t;
 }

@@ -102,9 +102,9 @@ __device__ __forceinline__ void quantize_exchange_f32(QuantStage& st, u32x4_t c0
 __global__ __launch_bounds__(kThreads) void nf4_quantize_kernel(NF4ConvArgs a)
 {
     // one copy of the round-to-nearest bin table per wave (the bin from one
-    // fma, as in the engine's short calls): a wave fills its own and reads it
-    // after its writes (one wave's LDS accesses complete in order), so the
-    // waves of a workgroup never wait for each other
+    // fma): a wave fills its own and reads it after its writes (one wave's LDS
+    // accesses complete in order), so the waves of a workgroup never wait for
+    // each other
     __shared__ NF4Bin wave_bins[kThreads / 64][kNF4RoundBins];
     NF4Bin* bins = wave_bins[threadIdx.x >> 6];
     const uint32_t lane = threadIdx.x & 63u;

@@ -139,7 +139,7 @@ __device__ __forceinline__ void nf4_requant_round(const NF4Bin* bins, uint32_t v
         for (int j = 7; j >= 0; --j) {
             const float x = w[j] * r;
             const uint32_t t = __float_as_uint(__builtin_fmaf(x, 64.0f, kNF4BinMagic));
-            code(j, x, (t << 4) - (kNF4BinBase << 4));  // 16 (t - base) = 16 b
+            code(j, x, (t << 3) - (kNF4BinBase << 3));  // 8 (t - base) = 8 b
         }
     } else {
         const float r = m > 0.0f ? 1.0f / m : 0.0f;
@@ -148,7 +148,7 @@ __device__ __forceinline__ void nf4_requant_round(const NF4Bin* bins, uint32_t v
             const float x = w[j] * r;
             const float xs = x == x ? x : -2.0f;
             const int k = int(__float_as_uint(__builtin_fmaf(xs, 64.0f, kNF4BinMagic))) - int(kNF4BinBase);
-            code(j, x, uint32_t(k < 0 ? 0 : (k > kNF4RoundBins - 1 ? kNF4RoundBins - 1 : k)) << 4);
+            code(j, x, uint32_t(k < 0 ? 0 : (k > kNF4RoundBins - 1 ? kNF4RoundBins - 1 : k)) << 3);
         }
     }
     packed = partial_wave(valid) ? p & nf4_nibble_mask(valid) : p;

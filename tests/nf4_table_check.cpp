@@ -46,13 +46,13 @@ static uint32_t code_floor(float x)
 }
 
 // round-to-nearest table, fast lookup: t = fl32(64 x + magic) with one
-// rounding; entry offset 16 (t - base)
+// rounding; entry offset 8 (t - base)
 static uint32_t code_fast(float x)
 {
     const uint32_t t = bits(std::fmaf(x, 64.0f, mezo::kNF4BinMagic));
-    const uint32_t off = (t << 4) - (mezo::kNF4BinBase << 4);
-    if (off % 16 != 0 || off / 16 >= uint32_t(kNF4RoundBins)) return 99;  // would read past the table
-    const mezo::NF4Bin& e = kNF4RoundTable.bin[off / 16];
+    const uint32_t off = (t << 3) - (mezo::kNF4BinBase << 3);
+    if (off % 8 != 0 || off / 8 >= uint32_t(kNF4RoundBins)) return 99;  // would read past the table
+    const mezo::NF4Bin& e = kNF4RoundTable.bin[off / 8];
     return e.lo + (x > e.mid ? 1u : 0u);
 }
 
