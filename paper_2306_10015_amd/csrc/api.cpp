@@ -349,11 +349,15 @@ int use_entry(mezo_paramset* ps, hipStream_t stream, mezo_paramset::Use*& out)
 }
 
 // Sets from here on have a call's last launch complete the entry's event
-// itself; on smaller ones it is recorded behind the launch. On the 125M fp32
-// set the launch's own event takes one sample's sweeps from 455.7 to 447.2 us
-// and the checksum from 84.9 to 82.2. On 1M elements, where the host sets the
-// pace, thousands of such launches leave a new set's first pass at 180 us
-// against 70-110 (the runtime's bookkeeping of events it has yet to retire).
+// itself; on smaller ones it is recorded behind the launch. Recorded, own, us a
+// call: fp32 sweeps back to back, 4M 11.3, 8.3; 16M 25.0, 22.3; 32M 44.9, 42.1;
+// 64M 85.1, 82.2; 128M 164.9, 162.2; bf16 and NF4 gain as much, checksums 2.8 at
+// every size. A call that is waited for by itself loses 2: 4M 20.0, 21.6; 16M
+// 34.5, 36.4; 64M 94.3, 96.4. The line keeps small sets from what long bursts
+// leave behind, the runtime's many events: after seven times 10,000 calls with
+// no wait between them, on a set of a quarter or half the size, fp32 sweeps
+// of 4M took 12.3, 14.5; 8M 15.0, 18.5; 16M 24.7, 23.8; 32M 44.6, 45.7; 64M 84.8,
+// 81.8; a new 4M set's first pass 77, 190 (16M and up: alike).
 constexpr uint64_t kOwnEventElements = uint64_t(1) << 24;
 hipEvent_t own_event(const mezo_paramset* ps, const mezo_paramset::Use* use)
 {

@@ -270,7 +270,9 @@ hipError_t launch_blocks(const EngineArgs& args, uint32_t tiles, hipStream_t str
 // 16M elements 62.6 -> 59.3, 59.3, 63.7 us; 32M 117.9 -> 112.9, 112.1, 118.5;
 // 64M 230.9 -> 220.4, 217.7, 224.6; 128M 458.6 -> 445.5, 431.7, 425.7 (K = 64
 // on 16M: 452 -> 426, 432, 453). bf16 with 2, 4: 8M 35.1 -> 33.0, 34.1; 16M
-// 62.1 -> 58.4, 58.5; 32M 116.1 -> 109.1, 107.6; 64M 224.1 -> 210.8, 205.3.
+// 62.1 -> 58.4, 58.5; 32M 116.1 -> 109.1, 107.6; 64M 224.1 -> 210.8, 205.3 (300
+// thousand, one wave per SIMD, where nothing pairs: 11.2 -> 9.5, but K = 16
+// 12.9 -> 13.6).
 // Portable, fp32 with 1, 2: 16M 113.2 -> 89.2, 96.7; 128M 864 -> 680, 670;
 // bf16 gains from 2 at every size (4: 4-7% slower). One portable record on fp32
 // is bound by memory too and keeps 1 at every size: one group per lane without

@@ -5,9 +5,9 @@
 // In the conversions a lane owns 8 consecutive elements (one dword of codes);
 // the 8 lanes tid & ~7 .. tid | 7 own one 64-element block and share its
 // absmax, and values become codes through the 129-bin round-to-nearest table
-// of nf4.hpp. In the engine a lane owns 16 (4 lanes per block); codes become
-// values through a table of byte -> the values of its two codes, values become
-// codes through the row table of nf4.hpp.
+// of nf4.hpp. In the engine a lane owns 16 (4 lanes per block), or 8 on small
+// sets; codes become values through a table of byte -> the values of its two
+// codes, values become codes through the row table of nf4.hpp.
 #pragma once
 
 #include "engine.hpp"
@@ -306,7 +306,7 @@ __device__ __forceinline__ float max4(float m)
 // kExact: r correctly rounded and x = fl32(w r), as the rule states. Otherwise
 // (fast mode's calls of one and two records) r is v_rcp_f32's (within 1 ulp)
 // and x is the product unrounded: a code can differ from the rule's only where
-// x lies within about 2^-23 of a midpoint. In the usual case (every lane's a
+// x lies within about 2^-22 of a midpoint. In the usual case (every lane's a
 // in [2^-64, 2^64]) |x| <= 1 + 2^-22 and the row needs no clamp; otherwise the
 // wave takes the general division and clamps the row, a NaN x (0 * inf)
 // taking the lowest row like the comparisons it fails.

@@ -28,7 +28,7 @@ def test_more_than_one_gpu_is_refused():
 def test_instruction_mix(bench):
     assert sum(bench.INNER_LOOP_MIX.values()) == 62
     assert bench.INSTR_PER_PARAM_SEED == 15.5
-    # 8 transcendentals per block of 4 Gaussians issue on their own unit
+    # the yardstick leaves out the 8 transcendentals per block of 4 Gaussians
     assert bench.NONTRANS_PER_PARAM_SEED == 13.5
     assert bench.VALU_LANE_INSTR_PER_S == pytest.approx(157.3e12 / 4, rel=1e-3)
     assert bench.PARAM_SEED_PEAK == pytest.approx(2.9127e12, rel=1e-4)
