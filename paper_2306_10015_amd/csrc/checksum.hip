@@ -171,11 +171,14 @@ struct RunCursor {
 // another tensor. Groups that cross a tensor's end and the run's last, shorter
 // one read map and descriptors of all their tiles (mix_any_tiles): one tile at
 // a time instead, each waiting for its descriptor and its data, the 125M fp32
-// call took 82.6 against 79.7 us. Up to four last tiles go one at a time
-// all the same: that is all that small sets have, and there the long group's
-// code, run once, costs more than its loads save (calls on 1M elements fp32
-// and bf16 20.2 -> 18.6 and 20.1 -> 18.4 us, 100 thousand fp32 10.0 -> 8.3;
-// three tiles 20.3 -> 18.9, four 20.3 -> 19.1, from five on equal; 125M 79.7).
+// call took 82.6 against 79.7 us. Up to four last tiles, and the whole of a
+// run of up to six, go one at a time all the same: that is all that small sets
+// have, and there the long group's code, run once, costs more than its loads
+// save (group, one at a time, us: 100 thousand fp32 elements 10.0, 8.3; 1M fp32
+// 20.2, 18.6, bf16 20.1, 18.4; runs of 4 and 5 tiles 20.5, 19.4 and 20.4, 19.7;
+// of 5 and 6 20.6, 19.9 and 20.6, 20.8; of 7 equal). In longer runs five last
+// tiles and more gain from the group (bf16, runs of 53 and 55 29.2, 29.8 and
+// 29.4, 31.0).
 // Few workgroups with many loads each stream faster than many with few:
 // against eight workgroups per CU with two tiles in flight, the 125M fp32 set
 // took 0.093 -> 0.085 ms and the 6.7B bf16 set 1.96 -> 1.90 ms (paired runs,
@@ -188,7 +191,7 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
     constexpr uint64_t kEsz = 16 / kPer;
     constexpr uint64_t kTileElems = uint64_t(kThreads) * kPer;
     constexpr uint64_t kInFlight = 8;  // tiles whose loads a lane issues before mixing any
-    constexpr uint64_t kShortRun = 4;  // last tiles taken one at a time
+    constexpr uint64_t kShortRun = 6, kShortTail = 4;  // tiles of a run, last tiles: one at a time
     // chunk number of the lane's first chunk within its tile, times kChunkPos;
     // opaque from here on: otherwise the compiler folds uniform + lane
     // constant back into one per-lane 64-bit multiply in every tile
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
 #pragma unroll
                 for (uint64_t j = 0; j < kInFlight; ++j)
                     sum += mix_whole_tile(v[j], cpos + j * (2 * kThreads * kChunkPos), tmix, cpos_lane);
-            } else if (t + kShortRun >= t_end) {
+            } else if (t + (t == t0 ? kShortRun : kShortTail) >= t_end) {
                 for (uint64_t k = t; k < t_end; ++k) {
                     c.seek(k);
                     const uint64_t at = k - c.begin;

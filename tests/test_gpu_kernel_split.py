@@ -176,11 +176,13 @@ def test_list_kernels_of_large_sets(mz, dtype, tiles, gaussian):
 
 
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
-@pytest.mark.parametrize("spread", [1, 11])
+@pytest.mark.parametrize("spread", [1, 6, 7, 8, 11, 13, 14])
 def test_checksum_runs_across_tensor_ends(mz, orc, dtype, spread):
     """A workgroup's run of tiles in groups of eight: short tensors one after
-    another, in one group or several, between tensors of many tiles, runs that
-    are no multiple of eight, and a shard's chunk numbers."""
+    another, in one group or several, between tensors of many tiles, and a
+    shard's chunk numbers. The 512 workgroups' runs are of 0 to 1, 4 to 7, 10
+    to 11 and 13 to 16 tiles: short ones taken a tile at a time or in a group,
+    and long ones' last 2 to 8."""
     per = 1024 if dtype == synth.F32 else 2048
     sizes = list(SIZES)
     for i in range(spread):
