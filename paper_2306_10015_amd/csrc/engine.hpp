@@ -158,20 +158,24 @@ MEZO_SETPRIO(0)
 MEZO_SETPRIO(1)
 #undef MEZO_SETPRIO
 
-template <class T, int kN>
+template <bool kPhases = true, class T, int kN>
 __device__ __forceinline__ void issue_alone(T (&v)[kN])
 {
-    __builtin_amdgcn_sched_barrier(0);
-    setprio1(v);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kPhases) {
+        __builtin_amdgcn_sched_barrier(0);
+        setprio1(v);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
-template <class T, int kN>
+template <bool kPhases = true, class T, int kN>
 __device__ __forceinline__ void issue_paired(T (&v)[kN])
 {
-    __builtin_amdgcn_sched_barrier(0);
-    setprio0(v);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kPhases) {
+        __builtin_amdgcn_sched_barrier(0);
+        setprio0(v);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 // philox_words for kBlocks blocks of a lane, in issue phases: the wide
@@ -180,8 +184,8 @@ __device__ __forceinline__ void issue_paired(T (&v)[kN])
 // record and wave), so that a xor reading it can pair with one reading the
 // other from its scalar register: 237 -> 230 -> 225 cycles per block and wave
 // for the whole record (2 blocks; 4 blocks; 4 blocks with such keys), 251
-// before the phases.
-template <int kBlocks>
+// before the phases. kPhases false: the same, in the compiler's order.
+template <int kBlocks, bool kPhases = true>
 __device__ __forceinline__ void philox_blocks(const SeedUniform& u, const BlockPre (&b)[kBlocks],
                                               uint32_t (&x)[kBlocks][4])
 {
@@ -204,10 +208,10 @@ __device__ __forceinline__ void philox_blocks(const SeedUniform& u, const BlockP
     // end of round 1, and round 2 (its kMulA product is scalar)
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i) y1[i] = b[i].hi ^ u.kx;
-    issue_alone(y1);
+    issue_alone<kPhases>(y1);
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i) p1[i] = uint64_t(kMulB) * y1[i];
-    issue_paired(p1);
+    issue_paired<kPhases>(p1);
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i) {
         y[i] = (u.r2_hi ^ u.k1) ^ b[i].lo;
@@ -217,13 +221,13 @@ __device__ __forceinline__ void philox_blocks(const SeedUniform& u, const BlockP
     }
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-        issue_alone(y);
+        issue_alone<kPhases>(y);
 #pragma unroll
         for (int i = 0; i < kBlocks; ++i) {
             p[kBlocks + i] = uint64_t(kMulA) * y[kBlocks + i];
             p[i] = uint64_t(kMulB) * y[i];
         }
-        issue_paired(p);
+        issue_paired<kPhases>(p);
 #pragma unroll
         for (int i = 0; i < kBlocks; ++i) {
             y[kBlocks + i] = xor3(uint32_t(p[i] >> 32), x[i][1], ka[r]);
@@ -417,13 +421,13 @@ __device__ __forceinline__ Z4 gauss4_portable(uint32_t w0, uint32_t w1, uint32_t
 // first); the product differs from fma(c, z, +0) only in the sign of a zero
 // product, which changes theta + acc only for theta = -0 (a -0 result where
 // the accumulator's +0 gives +0).
-template <int kBlocks, bool kSet>
+template <int kBlocks, bool kSet, bool kPhases = true>
 __device__ __forceinline__ void noise_fast(const SeedUniform& u, float c, const BlockPre (&b)[kBlocks],
                                            float (&acc)[kBlocks][4])
 {
     constexpr float kTwoM24 = 0x1p-24f;
     uint32_t x[kBlocks][4];
-    philox_blocks<kBlocks>(u, b, x);
+    philox_blocks<kBlocks, kPhases>(u, b, x);
     uint32_t ta[2 * kBlocks];  // u1's 24 bits
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i) {
@@ -435,7 +439,7 @@ __device__ __forceinline__ void noise_fast(const SeedUniform& u, float c, const 
     // from the conversions on the wave stays at the raised priority: its
     // multiplies and adds pair with another wave's conversions or xors
     // (against lowering it for them: 2% faster)
-    issue_alone(ta);
+    issue_alone<kPhases>(ta);
     float f[kBlocks][4];
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i) {
@@ -451,7 +455,7 @@ __device__ __forceinline__ void noise_fast(const SeedUniform& u, float c, const 
             f[i][2 * p] = __builtin_fmaf(f[i][2 * p], kTwoM24, kTwoM24);  // u1
             f[i][2 * p + 1] = f[i][2 * p + 1] * kTwoM24;                  // u2
         }
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kPhases) __builtin_amdgcn_sched_barrier(0);
     float r[kBlocks][2], cs[kBlocks][2], sn[kBlocks][2];
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i)
@@ -468,7 +472,7 @@ __device__ __forceinline__ void noise_fast(const SeedUniform& u, float c, const 
     for (int i = 0; i < kBlocks; ++i)
 #pragma unroll
         for (int p = 0; p < 2; ++p) r[i][p] = __builtin_amdgcn_sqrtf(-r[i][p]);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kPhases) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i)
 #pragma unroll

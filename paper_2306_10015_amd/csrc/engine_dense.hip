@@ -212,8 +212,11 @@ __global__ __launch_bounds__(kThreads) void engine_sweep_kernel(EngineArgs a)
     tile.store(t.d.data, t.d.numel, t.local, t.full);
 }
 
-// Any record list, kLanes lanes per tile.
-template <bool kInline, uint32_t kDtype, bool kPortable, int kLanes>
+// Any record list of one record or more, kLanes lanes per tile. Without issue
+// phases (launch_list) each record's words are read while the one before is
+// worked on; with them other waves hide the read, and reading early costs (12M
+// bf16 elements, portable, K = 64: 448 -> 475 us).
+template <bool kInline, uint32_t kDtype, bool kPortable, int kLanes, bool kPhases>
 __global__ __launch_bounds__(kLanes) void engine_kernel(EngineArgs a)
 {
     using Tile = LaneTile<kDtype, kLanes>;
@@ -230,37 +233,52 @@ __global__ __launch_bounds__(kLanes) void engine_kernel(EngineArgs a)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
     };
-    const auto accumulate = [&](uint32_t r) {
-        const SeedRec rec = rec_at<kInline>(a, r);
+    const auto accumulate = [&](const SeedRec& rec) {
         const SeedUniform u = seed_uniform(rec, t.d.tensor_id);
         if constexpr (kPortable)
             noise_portable<kBlocks, false>(u, rec.coef, pre, acc);
         else
-            noise_fast<kBlocks, false>(u, rec.coef, pre, acc);
+            noise_fast<kBlocks, false, kPhases>(u, rec.coef, pre, acc);
     };
     clear();
     // the last record ends the call's last step: peeled off the loop, it
     // needs no reset of acc afterwards
-    for (uint32_t r = 0; r + 1 < a.n_rec; ++r) {
-        accumulate(r);
-        if (rec_at<kInline>(a, r).last) {
-            tile.step_end(acc);
-            clear();
+    if constexpr (kPhases) {
+        for (uint32_t r = 0; r + 1 < a.n_rec; ++r) {
+            accumulate(rec_at<kInline>(a, r));
+            if (rec_at<kInline>(a, r).last) {
+                tile.step_end(acc);
+                clear();
+            }
         }
-    }
-    if (a.n_rec > 0) {
-        accumulate(a.n_rec - 1);
+        if (a.n_rec > 0) {
+            accumulate(rec_at<kInline>(a, a.n_rec - 1));
+            tile.step_end(acc);
+        }
+    } else {
+        SeedRec rec = rec_at<kInline>(a, 0);
+        for (uint32_t r = 1; r < a.n_rec; ++r) {
+            const SeedRec next = rec_at<kInline>(a, r);
+            accumulate(rec);
+            if (rec.last) {
+                tile.step_end(acc);
+                clear();
+            }
+            rec = next;
+        }
+        accumulate(rec);
         tile.step_end(acc);
     }
     tile.store(t.d.data, t.d.numel, t.local, t.full);
 }
 
 namespace {
-template <bool kInline, uint32_t kDtype, bool kPortable, int kBlocks>
+template <bool kInline, uint32_t kDtype, bool kPortable, int kBlocks, bool kPhases = true>
 hipError_t launch_blocks(const EngineArgs& args, uint32_t tiles, hipStream_t stream)
 {
     constexpr int kLanes = int(kThreads * Layout<kDtype>::kPerGroup / 4) / kBlocks;
-    return launch1(engine_kernel<kInline, kDtype, kPortable, kLanes>, tiles, kLanes, stream, args, args.done);
+    return launch1(engine_kernel<kInline, kDtype, kPortable, kLanes, kPhases>, tiles, kLanes, stream, args,
+                   args.done);
 }
 
 // How many Philox blocks a lane of a list launch takes. More blocks make
@@ -270,14 +288,20 @@ hipError_t launch_blocks(const EngineArgs& args, uint32_t tiles, hipStream_t str
 // 16M elements 62.6 -> 59.3, 59.3, 63.7 us; 32M 117.9 -> 112.9, 112.1, 118.5;
 // 64M 230.9 -> 220.4, 217.7, 224.6; 128M 458.6 -> 445.5, 431.7, 425.7 (K = 64
 // on 16M: 452 -> 426, 432, 453). bf16 with 2, 4: 8M 35.1 -> 33.0, 34.1; 16M
-// 62.1 -> 58.4, 58.5; 32M 116.1 -> 109.1, 107.6; 64M 224.1 -> 210.8, 205.3 (300
-// thousand, one wave per SIMD, where nothing pairs: 11.2 -> 9.5, but K = 16
-// 12.9 -> 13.6).
+// 62.1 -> 58.4, 58.5; 32M 116.1 -> 109.1, 107.6; 64M 224.1 -> 210.8, 205.3.
 // Portable, fp32 with 1, 2: 16M 113.2 -> 89.2, 96.7; 128M 864 -> 680, 670;
 // bf16 gains from 2 at every size (4: 4-7% slower). One portable record on fp32
 // is bound by memory too and keeps 1 at every size: one group per lane without
 // phases, 1, 2: 130M 169.9, 165.9, 169.4 us; 300M 383.5, 378.3, 390.0; 520M
 // 662, 654, 683 (two records: 520M 1039, 878, 839).
+// Fast mode on up to 256 tiles, a workgroup per CU and a wave per SIMD, goes
+// without phases: nothing pairs there, and the phases only keep the wave's own
+// instructions apart. As above (no phases, one group per lane), with phases,
+// without them and with the next record read early: 300 thousand bf16 elements
+// K = 16 12.8, 13.6, 12.4 us, K = 32 20.5, 22.0, 19.9, K = 64 47.0, 47.6, 45.3;
+// 255 thousand fp32 K = 32 18.1, 18.3, 16.1. From 257 tiles on two waves share
+// a SIMD: 600 thousand bf16 K = 32 23.9, 22.4, 23.3.
+constexpr uint32_t kTilesPhased = 257;
 constexpr uint32_t kTilesF32For2 = 24u << 10, kTilesF32For4 = 96u << 10, kTilesBF16For4 = 8u << 10;
 constexpr uint32_t kTilesF32PortableFor2 = 64u << 10;
 
@@ -290,13 +314,16 @@ hipError_t launch_list(const EngineArgs& args, uint32_t dtype, uint32_t tiles, h
                 return launch_blocks<kInline, kF32, true, 1>(args, tiles, stream);
             return launch_blocks<kInline, kF32, true, 2>(args, tiles, stream);
         } else {
+            if (tiles < kTilesPhased) return launch_blocks<kInline, kF32, false, 1, false>(args, tiles, stream);
             if (tiles < kTilesF32For2) return launch_blocks<kInline, kF32, false, 1>(args, tiles, stream);
             if (tiles < kTilesF32For4) return launch_blocks<kInline, kF32, false, 2>(args, tiles, stream);
             return launch_blocks<kInline, kF32, false, 4>(args, tiles, stream);
         }
     }
-    if constexpr (!kPortable)
+    if constexpr (!kPortable) {
+        if (tiles < kTilesPhased) return launch_blocks<kInline, kBF16, false, 2, false>(args, tiles, stream);
         if (tiles >= kTilesBF16For4) return launch_blocks<kInline, kBF16, false, 4>(args, tiles, stream);
+    }
     return launch_blocks<kInline, kBF16, kPortable, 2>(args, tiles, stream);
 }
 }  // namespace
