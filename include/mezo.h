@@ -130,9 +130,9 @@ extern "C" {
  *  FAST:     hardware transcendentals (v_log, v_sqrt, v_sin, v_cos); z within
  *            1e-6 * max|z| of the exact Box-Muller value; the default. On
  *            MEZO_NF4 storage the quantizer may also round differently (in
- *            calls of one or two records a hardware reciprocal; in their steps
- *            of one record the value plus the noise rounded once and the
- *            product w' r not at all): a code can then differ from the rule
+ *            calls of one or two records a hardware reciprocal and the product
+ *            w' r not rounded; in their steps of one record the value plus the
+ *            noise rounded once): a code can then differ from the rule
  *            stated with mezo_tensor_t only where x lies within about 2^-22
  *            of a midpoint, and the absmax by a few ulp.
  *  PORTABLE: z and the update from IEEE binary32 +, -, *, fma, correctly

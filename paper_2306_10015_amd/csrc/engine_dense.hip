@@ -25,10 +25,10 @@
 // vector issue: on large sets 4 Philox blocks per lane (fp32: 64 lanes per
 // tile, bf16: 128), so that the instructions of 4 blocks form issue phases
 // (engine.hpp) and the key schedule's moves are spread over them; fewer blocks
-// on smaller sets (launch_list): 2.54 -> 2.83e12 param-seeds/s
-// (K = 64 update of the 6.7B bf16 set, 167.6 -> 150.4 ms; K = 16 of the 1.3B
-// set 8.29 -> 7.52 ms; a 6 x 8 replay of the 125M fp32 set 2.37 -> 2.16 ms)
-// against one group per lane and no phases.
+// on smaller sets, and no phases on the smallest (launch_list): 2.54 -> 2.83e12
+// param-seeds/s (K = 64 update of the 6.7B bf16 set, 167.6 -> 150.4 ms; K = 16
+// of the 1.3B set 8.29 -> 7.52 ms; a 6 x 8 replay of the 125M fp32 set 2.37 ->
+// 2.16 ms) against one group per lane and no phases.
 #include "engine.hpp"
 #include "engine_launch.hpp"
 #include "launch.hpp"
