@@ -92,6 +92,33 @@ __device__ __forceinline__ u32x4_t load_ragged(uint64_t addr, uint32_t bytes)
     return u32x4_t{w[0], w[1], w[2], w[3]};
 }
 
+// The mixes of those of a lane's two chunks that exist in a tile of `bytes`
+// bytes (p0: its first chunk's number * kChunkPos).
+__device__ __forceinline__ uint64_t mix_present(u32x4_t v, uint32_t bytes, uint64_t p0, uint64_t tmix)
+{
+    const uint32_t off = threadIdx.x * 16u;
+    const uint64_t lo = uint64_t(v.x) | (uint64_t(v.y) << 32);
+    const uint64_t hi = uint64_t(v.z) | (uint64_t(v.w) << 32);
+    uint64_t sum = 0;
+    if (off < bytes) sum += fmix64(lo ^ p0 ^ tmix);
+    if (off + 8 < bytes) sum += fmix64(hi ^ (p0 + kChunkPos) ^ tmix);
+    return sum;
+}
+
+// The mixes of a lane's chunks of a tensor's last tile, of which `bytes` bytes
+// exist.
+template <uint32_t kDtype>
+__device__ __forceinline__ uint64_t mix_cut_tile(uint64_t addr, uint32_t bytes, uint64_t p0, uint64_t tmix)
+{
+    const uint32_t off = threadIdx.x * 16u;
+    u32x4_t v = {0u, 0u, 0u, 0u};
+    if (off + 16 <= bytes)
+        v = __builtin_nontemporal_load(reinterpret_cast<const gu32x4_t*>(addr) + threadIdx.x);
+    else if (off < bytes)
+        v = load_ragged<kDtype>(addr + off, bytes - off);
+    return mix_present(v, bytes, p0, tmix);
+}
+
 // The mixes of a lane's chunks of tiles t .. t + n - 1 (1 <= n <= kTiles) of
 // any tensors, each whole or cut by its tensor's end: the map entries of all
 // of them are read first, then their descriptors, then the data, so that the
@@ -127,11 +154,7 @@ __device__ __forceinline__ uint64_t mix_any_tiles(const ChecksumArgs& a, uint64_
 #pragma unroll
     for (uint32_t j = 0; j < kTiles; ++j) {
         if (off < bytes[j] && off + 16 > bytes[j]) v[j] = load_ragged<kDtype>(addr[j] + off, bytes[j] - off);
-        const uint64_t p0 = cpos[j] + cpos_lane;
-        const uint64_t lo = uint64_t(v[j].x) | (uint64_t(v[j].y) << 32);
-        const uint64_t hi = uint64_t(v[j].z) | (uint64_t(v[j].w) << 32);
-        if (off < bytes[j]) sum += fmix64(lo ^ p0 ^ tmix[j]);
-        if (off + 8 < bytes[j]) sum += fmix64(hi ^ (p0 + kChunkPos) ^ tmix[j]);
+        sum += mix_present(v[j], bytes[j], cpos[j] + cpos_lane, tmix[j]);
     }
     return sum;
 }
@@ -221,12 +244,14 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
                 for (uint64_t k = t; k < t_end; ++k) {
                     c.seek(k);
                     const uint64_t at = k - c.begin;
+                    const uint64_t cpos = (c.first * kEsz / 8 + 2 * at * kThreads) * kChunkPos;
+                    const uint64_t tmix = uint64_t(c.id) * kChunkTensor;
                     if ((at + 1) * kTileElems <= c.numel)
-                        sum += mix_whole_tile(load_whole_tile(c.data, at),
-                                              (c.first * kEsz / 8 + 2 * at * kThreads) * kChunkPos,
-                                              uint64_t(c.id) * kChunkTensor, cpos_lane);
+                        sum += mix_whole_tile(load_whole_tile(c.data, at), cpos, tmix, cpos_lane);
                     else
-                        sum += mix_any_tiles<kDtype, 1u>(a, k, 1u, cpos_lane);
+                        sum += mix_cut_tile<kDtype>(c.data + at * (kThreads * 16),
+                                                    uint32_t((c.numel - at * kTileElems) * kEsz), cpos + cpos_lane,
+                                                    tmix);
                 }
             } else {
                 const uint64_t n = t_end - t < kInFlight ? t_end - t : kInFlight;
