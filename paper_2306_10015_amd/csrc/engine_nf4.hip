@@ -127,8 +127,8 @@ __device__ __forceinline__ void block_pres(uint32_t blk, BlockPre (&pre)[kN])
 // first record, which saves zeroing the accumulators; the product can differ
 // from fma(c, z, +0) only in the sign of a zero, which no code depends on, +0
 // and -0 sharing the zero code's row) or acc += c z. The portable transform
-// takes two blocks at a time.
-template <bool kPortable, bool kSet, int kN>
+// takes two blocks at a time. kPhases: fast mode in issue phases (engine.hpp).
+template <bool kPortable, bool kSet, bool kPhases, int kN>
 __device__ __forceinline__ void noise(const SeedRec& rec, uint32_t tensor_id, const BlockPre (&pre)[kN],
                                       float (&acc)[kN][4])
 {
@@ -146,7 +146,7 @@ __device__ __forceinline__ void noise(const SeedRec& rec, uint32_t tensor_id, co
             for (int j = 0; j < 8; ++j) acc[h + (j >> 2)][j & 3] = a2[j >> 2][j & 3];
         }
     } else {
-        noise_fast<kN, kSet>(u, c, pre, acc);
+        noise_fast<kN, kSet, kPhases>(u, c, pre, acc);
     }
 }
 
@@ -174,7 +174,7 @@ __device__ __forceinline__ void sweep_tile(const EngineArgs& a, NF4Tile<kDwords>
     BlockPre pre[2 * kDwords];
     block_pres(t.block(), pre);
     float acc[2 * kDwords][4];
-    noise<kPortable, true>(a.inl[0], t.d.tensor_id, pre, acc);
+    noise<kPortable, true, true>(a.inl[0], t.d.tensor_id, pre, acc);
     copy.store(lds);
     step_end<!kPortable, kPortable, kFull>(lds, t, acc);
     t.template store<kFull>();
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_sweep_kernel(En
 // A tile through a call of two records: a restore fused with the next
 // perturbation, or an update of two records in one step. With no records (out
 // of place with nothing to apply) the tile is copied.
-template <bool kPortable, bool kFull, int kDwords>
+template <bool kPortable, bool kFull, int kDwords, bool kPhases>
 __device__ __forceinline__ void short_tile(const EngineArgs& a, NF4Tile<kDwords>& t, NF4Lds& lds)
 {
     t.template load<kFull>();
@@ -205,14 +205,14 @@ __device__ __forceinline__ void short_tile(const EngineArgs& a, NF4Tile<kDwords>
         BlockPre pre[2 * kDwords];
         block_pres(t.block(), pre);
         float acc[2 * kDwords][4];
-        noise<kPortable, true>(a.inl[0], t.d.tensor_id, pre, acc);
+        noise<kPortable, true, kPhases>(a.inl[0], t.d.tensor_id, pre, acc);
         copy.store(lds);
         if (a.inl[0].last) {
             step_end<!kPortable, kPortable, kFull>(lds, t, acc);
-            noise<kPortable, true>(a.inl[1], t.d.tensor_id, pre, acc);
+            noise<kPortable, true, kPhases>(a.inl[1], t.d.tensor_id, pre, acc);
             step_end<!kPortable, kPortable, kFull>(lds, t, acc);
         } else {  // two records in one step: their sum, one rounding
-            noise<kPortable, false>(a.inl[1], t.d.tensor_id, pre, acc);
+            noise<kPortable, false, kPhases>(a.inl[1], t.d.tensor_id, pre, acc);
             step_end<false, kPortable, kFull>(lds, t, acc);
         }
     }
@@ -220,21 +220,21 @@ __device__ __forceinline__ void short_tile(const EngineArgs& a, NF4Tile<kDwords>
 }
 
 // A call of two records (inline), or of none.
-template <bool kPortable, int kDwords>
+template <bool kPortable, int kDwords, bool kPhases>
 __global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_short_kernel(EngineArgs a)
 {
     __shared__ NF4Lds lds;
     NF4Tile<kDwords> t(a);
     if (t.whole())
-        short_tile<kPortable, true>(a, t, lds);
+        short_tile<kPortable, true, kDwords, kPhases>(a, t, lds);
     else
-        short_tile<kPortable, false>(a, t, lds);
+        short_tile<kPortable, false, kDwords, kPhases>(a, t, lds);
 }
 
 // Record lists of more than two records: one loop over the records. The
 // quantizer follows the rule exactly in both modes (its cost is spread over
 // the records).
-template <bool kInline, bool kPortable, int kDwords>
+template <bool kInline, bool kPortable, int kDwords, bool kPhases>
 __global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_kernel(EngineArgs a)
 {
     __shared__ NF4Lds lds;
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_kernel(EngineAr
     // every record list ends a step with its last record
     for (uint32_t r = 0; r < a.n_rec; ++r) {
         const SeedRec rec = rec_at<kInline>(a, r);
-        noise<kPortable, false>(rec, t.d.tensor_id, pre, acc);
+        noise<kPortable, false, kPhases>(rec, t.d.tensor_id, pre, acc);
         if (rec.last) {
             step_end<false, true, false>(lds, t, acc);
             clear();
@@ -270,17 +270,18 @@ __global__ __launch_bounds__(kNF4Lanes<kDwords>) void engine_nf4_kernel(EngineAr
 }
 
 namespace {
-template <bool kPortable, int kDwords>
+template <bool kPortable, int kDwords, bool kPhases = true>
 hipError_t launch_variant(const EngineArgs& args, uint32_t tiles, hipStream_t stream)
 {
     constexpr int kLanes = kNF4Lanes<kDwords>;
     // (two dwords in portable mode are for short lists: launch_dwords)
     if constexpr (!(kPortable && kDwords == 2))
         if (args.n_rec > kInlineRecs)
-            return launch1(engine_nf4_kernel<false, kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
+            return launch1(engine_nf4_kernel<false, kPortable, kDwords, kPhases>, tiles, kLanes, stream, args, args.done);
     if (args.n_rec == 1) return launch1(engine_nf4_sweep_kernel<kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
-    if (args.n_rec <= 2) return launch1(engine_nf4_short_kernel<kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
-    return launch1(engine_nf4_kernel<true, kPortable, kDwords>, tiles, kLanes, stream, args, args.done);
+    if (args.n_rec <= 2)
+        return launch1(engine_nf4_short_kernel<kPortable, kDwords, kPhases>, tiles, kLanes, stream, args, args.done);
+    return launch1(engine_nf4_kernel<true, kPortable, kDwords, kPhases>, tiles, kLanes, stream, args, args.done);
 }
 
 // Two code dwords per lane from kTilesNF4For2 tiles on, as on dense storage
@@ -292,6 +293,12 @@ hipError_t launch_variant(const EngineArgs& args, uint32_t tiles, hipStream_t st
 // (16M: 122.5 -> 85.6, 89.2; 64M 453.5 -> 315.4, 318.5; K = 64 on 128M 6741 ->
 // 4744, 4867), but for short lists on large sets (one record on 1.3B: 1440 ->
 // 1097, 1047; three on 128M 363.5 -> 266.1, 262.9).
+// Fast lists and two-record calls on up to 256 tiles go without issue phases
+// (one wave per SIMD: engine_dense.hip). 250 thousand elements in a graph, before
+// the phases, with, without: K = 32 16.6, 16.9, 15.9 us; K = 8 6.14, 6.22, 6.04;
+// K = 2 3.46, 3.60, 3.50. 1M elements, two waves per SIMD: K = 32 21.2, 19.4,
+// 22.0.
+constexpr uint32_t kTilesNF4Phased = 257;
 constexpr uint32_t kTilesNF4For2 = 12u << 10, kTilesNF4PortableFor2 = 48u << 10, kRecsNF4PortableFor2 = 4;
 static_assert(kRecsNF4PortableFor2 <= kInlineRecs, "launch_variant has no staged kernel for these");
 
@@ -300,6 +307,7 @@ hipError_t launch_dwords(const EngineArgs& args, bool portable, uint32_t tiles, 
     if (portable && tiles >= kTilesNF4PortableFor2 && args.n_rec <= kRecsNF4PortableFor2)
         return launch_variant<true, 2>(args, tiles, stream);
     if (portable) return launch_variant<true, 1>(args, tiles, stream);
+    if (tiles < kTilesNF4Phased) return launch_variant<false, 1, false>(args, tiles, stream);
     if (tiles < kTilesNF4For2) return launch_variant<false, 1>(args, tiles, stream);
     return launch_variant<false, 2>(args, tiles, stream);
 }

@@ -128,7 +128,7 @@ def test_list_kernel_against_the_oracle(mz, orc, dtype, K):
 @pytest.mark.parametrize("dtype,tiles,gaussian", [
     # one set on each side of the sizes at which the kernel changes: issue
     # phases, more blocks per lane
-    (synth.F32, 257, "fast"), (synth.BF16, 257, "fast"),
+    (synth.F32, 257, "fast"), (synth.BF16, 257, "fast"), (synth.NF4, 257, "fast"),
     (synth.F32, 24 * 1024, "fast"), (synth.F32, 96 * 1024, "fast"), (synth.BF16, 8 * 1024, "fast"),
     (synth.F32, 64 * 1024, "portable"), (synth.NF4, 12 * 1024, "fast"), (synth.NF4, 48 * 1024, "portable")])
 def test_list_kernels_of_large_sets(mz, dtype, tiles, gaussian):
