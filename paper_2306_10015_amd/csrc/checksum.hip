@@ -194,27 +194,26 @@ struct RunCursor {
 // another tensor. Groups that cross a tensor's end and the run's last, shorter
 // one read map and descriptors of all their tiles (mix_any_tiles): one tile at
 // a time instead, each waiting for its descriptor and its data, the 125M fp32
-// call took 82.6 against 79.7 us. Up to four last tiles, and the whole of a
-// run of up to six, go one at a time all the same: that is all that small sets
-// have, and there the long group's code, run once, costs more than its loads
-// save (group, one at a time, us: 100 thousand fp32 elements 10.0, 8.3; 1M fp32
-// 20.2, 18.6, bf16 20.1, 18.4; runs of 4 and 5 tiles 20.5, 19.4 and 20.4, 19.7;
-// of 5 and 6 20.6, 19.9 and 20.6, 20.8; of 7 equal). In longer runs five last
-// tiles and more gain from the group (bf16, runs of 53 and 55 29.2, 29.8 and
-// 29.4, 31.0).
+// call took 82.6 against 79.7 us. Up to four last tiles go one at a time all the
+// same; five and more gain from the group (bf16, runs of 53 and 55 tiles 29.8,
+// 31.0 -> 29.2, 29.4). kShort: runs of up to six tiles (fp32: seven), all that
+// small sets have, go one at a time as a whole, in a kernel without the groups'
+// code, which run once costs more than its loads save (group, one at a time, us:
+// 100 thousand fp32 elements 10.0, 8.2; 1M fp32 20.2, 18.3, bf16 20.1, 17.7; runs
+// of 4 and 5 tiles fp32 20.4, 19.1, bf16 20.3, 19.3; of 6 and 7 fp32 20.6, 20.1).
 // Few workgroups with many loads each stream faster than many with few:
 // against eight workgroups per CU with two tiles in flight, the 125M fp32 set
 // took 0.093 -> 0.085 ms and the 6.7B bf16 set 1.96 -> 1.90 ms (paired runs,
 // checksums identical; one workgroup per CU or sixteen tiles in flight were
 // slower).
-template <uint32_t kDtype>
+template <uint32_t kDtype, bool kShort>
 __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
 {
     constexpr uint64_t kPer = Layout<kDtype>::kPerGroup;
     constexpr uint64_t kEsz = 16 / kPer;
     constexpr uint64_t kTileElems = uint64_t(kThreads) * kPer;
-    constexpr uint64_t kInFlight = 8;  // tiles whose loads a lane issues before mixing any
-    constexpr uint64_t kShortRun = 6, kShortTail = 4;  // tiles of a run, last tiles: one at a time
+    constexpr uint64_t kInFlight = 8;   // tiles whose loads a lane issues before mixing any
+    constexpr uint64_t kShortTail = 4;  // last tiles taken one at a time
     // chunk number of the lane's first chunk within its tile, times kChunkPos;
     // opaque from here on: otherwise the compiler folds uniform + lane
     // constant back into one per-lane 64-bit multiply in every tile
@@ -228,34 +227,40 @@ __global__ __launch_bounds__(kThreads) void checksum_kernel(ChecksumArgs a)
         RunCursor<kTileElems> c;
         c.tensors = a.tensors;
         c.load(a.tile_tensor[t0]);
-        for (uint64_t t = t0; t < t_end; t += kInFlight) {
-            if (t >= c.end) c.load(a.tile_tensor[t]);
-            const uint64_t local = t - c.begin;
-            if (t + kInFlight <= t_end && (local + kInFlight) * kTileElems <= c.numel) {  // uniform
-                u32x4_t v[kInFlight];
-#pragma unroll
-                for (uint64_t j = 0; j < kInFlight; ++j) v[j] = load_whole_tile(c.data, local + j);
-                const uint64_t cpos = (c.first * kEsz / 8 + 2 * local * kThreads) * kChunkPos;
+        const auto one_at_a_time = [&](uint64_t t) {  // tiles t .. t_end - 1
+            for (; t < t_end; ++t) {
+                c.seek(t);
+                const uint64_t at = t - c.begin;
+                const uint64_t cpos = (c.first * kEsz / 8 + 2 * at * kThreads) * kChunkPos;
                 const uint64_t tmix = uint64_t(c.id) * kChunkTensor;
+                if ((at + 1) * kTileElems <= c.numel)
+                    sum += mix_whole_tile(load_whole_tile(c.data, at), cpos, tmix, cpos_lane);
+                else
+                    sum += mix_cut_tile<kDtype>(c.data + at * (kThreads * 16),
+                                                uint32_t((c.numel - at * kTileElems) * kEsz), cpos + cpos_lane, tmix);
+            }
+        };
+        if constexpr (kShort) {
+            one_at_a_time(t0);
+        } else {
+            for (uint64_t t = t0; t < t_end; t += kInFlight) {
+                if (t >= c.end) c.load(a.tile_tensor[t]);
+                const uint64_t local = t - c.begin;
+                if (t + kInFlight <= t_end && (local + kInFlight) * kTileElems <= c.numel) {  // uniform
+                    u32x4_t v[kInFlight];
 #pragma unroll
-                for (uint64_t j = 0; j < kInFlight; ++j)
-                    sum += mix_whole_tile(v[j], cpos + j * (2 * kThreads * kChunkPos), tmix, cpos_lane);
-            } else if (t + (t == t0 ? kShortRun : kShortTail) >= t_end) {
-                for (uint64_t k = t; k < t_end; ++k) {
-                    c.seek(k);
-                    const uint64_t at = k - c.begin;
-                    const uint64_t cpos = (c.first * kEsz / 8 + 2 * at * kThreads) * kChunkPos;
+                    for (uint64_t j = 0; j < kInFlight; ++j) v[j] = load_whole_tile(c.data, local + j);
+                    const uint64_t cpos = (c.first * kEsz / 8 + 2 * local * kThreads) * kChunkPos;
                     const uint64_t tmix = uint64_t(c.id) * kChunkTensor;
-                    if ((at + 1) * kTileElems <= c.numel)
-                        sum += mix_whole_tile(load_whole_tile(c.data, at), cpos, tmix, cpos_lane);
-                    else
-                        sum += mix_cut_tile<kDtype>(c.data + at * (kThreads * 16),
-                                                    uint32_t((c.numel - at * kTileElems) * kEsz), cpos + cpos_lane,
-                                                    tmix);
+#pragma unroll
+                    for (uint64_t j = 0; j < kInFlight; ++j)
+                        sum += mix_whole_tile(v[j], cpos + j * (2 * kThreads * kChunkPos), tmix, cpos_lane);
+                } else if (t + kShortTail >= t_end) {
+                    one_at_a_time(t);
+                } else {
+                    const uint64_t n = t_end - t < kInFlight ? t_end - t : kInFlight;
+                    sum += mix_any_tiles<kDtype, uint32_t(kInFlight)>(a, t, uint32_t(n), cpos_lane);
                 }
-            } else {
-                const uint64_t n = t_end - t < kInFlight ? t_end - t : kInFlight;
-                sum += mix_any_tiles<kDtype, uint32_t(kInFlight)>(a, t, uint32_t(n), cpos_lane);
             }
         }
     }
@@ -405,7 +410,8 @@ __global__ void zero_u64_kernel(unsigned long long* out)
 namespace {
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_cus[kMaxDevices];  // compute units per device, 0 = not yet asked
-
+// tiles of a workgroup's run up to which the kernel without groups takes it
+constexpr uint64_t kShortRunF32 = 7, kShortRunBF16 = 6;
 }  // namespace
 
 hipError_t launch_checksum(const ChecksumArgs* tables, const uint32_t* dtypes, int n_tables,
@@ -440,10 +446,13 @@ hipError_t launch_checksum(const ChecksumArgs* tables, const uint32_t* dtypes, i
         const uint64_t grid = need < cap ? need : cap;
         const uint32_t g = uint32_t(grid);
         const hipEvent_t done = i == last ? args.done : nullptr;
+        const bool brief = tables[i].total_tiles <= (dtypes[i] == kF32 ? kShortRunF32 : kShortRunBF16) * grid;
         if (dtypes[i] == kF32)
-            e = launch1(checksum_kernel<kF32>, g, kThreads, stream, args, done);
+            e = launch1(brief ? checksum_kernel<kF32, true> : checksum_kernel<kF32, false>, g, kThreads, stream, args,
+                        done);
         else if (dtypes[i] == kBF16)
-            e = launch1(checksum_kernel<kBF16>, g, kThreads, stream, args, done);
+            e = launch1(brief ? checksum_kernel<kBF16, true> : checksum_kernel<kBF16, false>, g, kThreads, stream, args,
+                        done);
         else
             e = launch1(checksum_nf4_kernel, g, kThreads, stream, args, done);
         if (e != hipSuccess) return e;
