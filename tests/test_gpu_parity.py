@@ -749,7 +749,9 @@ def test_more_streams_than_tracked(mz, orc):
 def test_destroy_waits_for_work_on_every_stream(mz):
     """A paramset used on two streams: destroy returns only after the long
     replay on the first stream has finished, not just the short perturb
-    enqueued last on the second."""
+    enqueued last on the second. (Freeing device memory waits for the device
+    by itself: that destroy's own waits are right, the host check on the CPU
+    shows, tests/sanitize/abi_host_check.c, check_waits.)"""
     import torch
     w = synth.WORKLOADS["opt125m"]
     hosts = [synth.theta0_tensor((1 << 24,), synth.F32, 0, 1)]
